@@ -113,6 +113,11 @@ __device__ __forceinline__ long long xcd_block(long long b, long long nb) {
     return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
+__device__ __forceinline__ unsigned xcd_block32(unsigned b, unsigned nb) {
+    const unsigned q = nb / 8, r = nb % 8, x = b % 8, i = b / 8;
+    return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
+}
+
 // Upper bound on the grid of a persistent multi-problem launch.
 constexpr long long PERSISTENT_BLOCKS = 2048;
 

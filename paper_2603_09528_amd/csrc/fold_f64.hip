@@ -1,0 +1,106 @@
+// Instantiations of the FP64 transforms of mirror-symmetric directions, and
+// the choice of their tile.
+#include <algorithm>
+
+#include "fold_impl.h"
+
+namespace tpt {
+
+bool fold_fits(int n, int nx, bool ylines) {
+    const long long hp = ((n + 1) / 2 + FOLD_ROWS - 1) / FOLD_ROWS * FOLD_ROWS;
+    const long long kp = ((n + 1) / 2 + FOLD_COLS - 1) / FOLD_COLS * FOLD_COLS;
+    const long long lim = 0x7fffff00LL / 8;
+    if (n < FOLD_MIN_N || 2 * hp * kp > lim) return false;
+    // a tile's lines: 128 x lines, or columns of at most 128 / nx + 2 slabs
+    return ylines ? (long long)nx * n * (128 / nx + 2) <= lim : 128LL * n <= lim;
+}
+
+static void fold_dims(const FoldDesc& g, int shape, int* ph, int* dn) {
+    *ph = shape == FOLD_64x128 ? 64 : shape == FOLD_32x128 ? 32 : 16;
+    *dn = shape == FOLD_16x64 || (shape == FOLD_64x128 && g.X) ? 64 : 128;
+}
+
+long long fold_tiles(FoldDesc& g, int shape) {
+    int ph, dn;
+    fold_dims(g, shape, &ph, &dn);
+    g.tiles_p = (g.h + ph - 1) / ph;
+    return (long long)g.tiles_p * ((g.lines + dn - 1) / dn);
+}
+
+// Relative time of a launch of `tiles` tiles: what the compute unit with most
+// tiles has to do, over the rate the shape reaches when it has enough.  The
+// padding of h to whole tiles and the idle units of a last round are in the
+// tile count.  Rates from 256^3, 448 x 320 x 288 and 640 x 640 x 64 (remainders:
+// 44, 40 and 22 TFLOP/s useful for 64 x 64, 32 x 128 and 16 x 64; without:
+// 46, 45 and 36); small cases it decides: 192 x 160 x 128, x lines, 31 us in
+// 32 x 128 against 36 in 64 x 64 (remainders) and 26 against 38 in 64 x 128;
+// 64 x 48 x 64, 6-8 us in 16 x 64 against 8 us.
+static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
+    static const double rate[2][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.92, 0.55}};
+    int ph, dn;
+    fold_dims(g, shape, &ph, &dn);
+    return (double)((tiles + 255) / 256) * ph * dn / rate[g.X ? 1 : 0][shape];
+}
+
+int fold_shape(const FoldDesc* g, int count) {
+    int best = 0;
+    double cost = 0.0;
+    for (int v = 0; v < FOLD_NSHAPE; ++v) {
+        long long tiles = 0;
+        for (int i = 0; i < count; ++i) {
+            FoldDesc t = g[i];
+            tiles += fold_tiles(t, v);
+        }
+        const double c = fold_cost(g[0], v, tiles);
+        if (v == 0 || c < cost) {
+            best = v;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+long long fold_grid(int shape, bool corr, long long total) {
+    const long long percu = shape == FOLD_64x128 || (shape == FOLD_32x128 && corr) ? 2 : shape == FOLD_32x128 ? 3 : 5;
+    return std::min(total, 256 * percu);
+}
+
+std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long total) {
+    std::vector<unsigned> c;
+    size_t i = 0;
+    for (long long v = 0; v < total; v += FOLD_COARSE) {
+        while (i + 1 < g.size() && g[i + 1].block_begin <= v) ++i;
+        c.push_back((unsigned)i);
+    }
+    return c;
+}
+
+hipError_t launch_fold(FoldDesc g, int prec, hipStream_t s) {
+    const int shape = fold_shape(&g, 1);
+    const long long total = fold_tiles(g, shape);
+    return prec == GP_F64 ? launch_fold_f64(g, nullptr, total, shape, s) : launch_fold_f32(g, nullptr, total, shape, s);
+}
+
+hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int prec, int shape,
+                             hipStream_t s) {
+    return prec == GP_F64 ? launch_fold_f64(rep, &list, total, shape, s) : launch_fold_f32(rep, &list, total, shape, s);
+}
+
+template <bool CORR>
+static hipError_t launch_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s) {
+    typedef double D;
+    constexpr int E = EPI_STORE;
+    if (g.ylines)
+        return g.inverse ? launch_fold_typed<D, D, D, E, true, true, CORR>(g, list, total, shape, s)
+                         : launch_fold_typed<D, D, D, E, true, false, CORR>(g, list, total, shape, s);
+    return g.inverse ? launch_fold_typed<D, D, D, E, false, true, CORR>(g, list, total, shape, s)
+                     : launch_fold_typed<D, D, D, E, false, false, CORR>(g, list, total, shape, s);
+}
+
+hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s) {
+    if (g.tin != DT_F64 || g.tout != DT_F64 || g.epi != EPI_STORE) return hipErrorInvalidValue;
+    return g.X ? launch_f64<true>(g, list, total, shape, s)
+               : launch_f64<false>(g, list, total, shape, s);
+}
+
+}  // namespace tpt

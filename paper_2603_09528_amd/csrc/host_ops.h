@@ -19,6 +19,11 @@ struct Op1D {
     bool uniform = false;    // all control volumes and neighbour distances equal
     int bc_lo = BC_N, bc_hi = BC_N, loc = LOC_C;
     std::vector<double> a, b, c, vol;
+    // The operator is its own mirror image (i -> n-1-i) up to the rounding of
+    // the face coordinates: the same condition at both walls on faces
+    // symmetric about the middle, or a uniform periodic direction.  exact:
+    // to the last bit, or a uniform direction (closed-form basis).
+    bool mirror = false, mirror_exact = false;
 };
 
 // Returns an empty string on success, else the reason.
@@ -35,5 +40,26 @@ struct Eig1D {
 };
 
 std::string eig_op1d(const Op1D& op, Eig1D& e);
+
+// A basis as products of half the size read it (fold_impl.h): h = (n + 1) / 2
+// pairs of an even and an odd vector, slot a holding even mode 2a and odd mode
+// 2a + 1 (even n) or 2a - 1 (odd n, whose slot 0 has no odd vector: then the
+// modes that come in nearly degenerate pairs share a slot).  The vectors of a
+// slot are eigenvectors v up to a rotation,
+//   v_even = c e + s o,  v_odd = -s e + c o,  (c, s) = rot[a],
+// that leaves e as symmetric and o as antisymmetric as possible.
+// fwd / inv: [2][hp][kp] main parts, fwd[par][a][k] and inv[par][k][a]; xfwd /
+// xinv: what is left, the antisymmetric part of e's row (par 0) and the
+// symmetric part of o's (par 1) (forward; inverse: the symmetric part of o and
+// the antisymmetric part of e).  The middle column of an odd n is halved in
+// fwd.  All zero beyond h.
+struct FoldBasis {
+    int hp = 0, kp = 0;
+    bool rotated = false;            // rot and xfwd / xinv are not trivial
+    std::vector<double> fwd, inv, xfwd, xinv, rot;
+};
+// Whether the basis splits like this with xfwd, xinv small enough for the
+// kernel's split of them (always for an exact mirror operator).
+bool fold_basis(const Op1D& op, const Eig1D& e, int hp, int kp, FoldBasis& f);
 
 }  // namespace tpt

@@ -30,11 +30,29 @@ const char* last_error_cstr();
 // Orientation: Qinv[p][i] = Q~[i][p] s_i (forward, Q^{-1} = Q~^T D^{1/2}) and
 // Q[i][p] = Q~[i][p] / s_i (inverse, Q = D^{-1/2} Q~), both row-major
 // [out][in] (Eq. q-from-tildeq).
+// What a plan applies to a direction, and so which device copies its basis
+// holds: a fast transform (tables only), two half-size products of a mirror
+// direction, or the dense product.
+enum BasisForm { BF_FAST = 0, BF_FOLD = 1, BF_DENSE = 2 };
 struct DirBasis {
     int device = 0;
     int n = 0;
-    Eig1D eig;                       // host eigen data
-    double* d_lam = nullptr;         // device eigenvalues
+    int form = BF_DENSE;
+    std::shared_ptr<const Eig1D> eig;  // host eigen data
+    double* d_lam = nullptr;         // device eigenvalues in the order of the modes of `form`
+    int null_pos = -1;               // position of the exact null vector in that order, or -1
+    // BF_FOLD: even and odd half bases, [2][hp][kp]
+    double* fd_qinv = nullptr;
+    double* fd_q = nullptr;
+    float* fs_qinv = nullptr;
+    float* fs_q = nullptr;
+    // remainders of bases symmetric only up to the rounding of the faces (bf16,
+    // scaled, FP64 plans) and the rotation of each slot; null otherwise
+    uint16_t* fx_qinv = nullptr;
+    uint16_t* fx_q = nullptr;
+    double2* f_rot = nullptr;
+    int hp = 0, kp = 0;
+    // BF_DENSE
     double* d_qinv = nullptr;        // FP64
     double* d_q = nullptr;
     float* s_qinv = nullptr;         // FP32 copies
@@ -44,7 +62,6 @@ struct DirBasis {
     uint16_t* h_q = nullptr;
     uint16_t* l_q = nullptr;
     int ldp = 0;
-    int fast_kind = -1;              // XformKind of the fast transform, -1 = none
     double2* d_twiddle = nullptr;    // e^{-2 pi i k/n}, k < n/2 (fast transform)
     double2* d_qtw = nullptr;        // e^{-i pi k/2n}, k <= n/2 (DCT, DST)
     double h = 0.0;                  // uniform spacing (analytic bases)
@@ -53,9 +70,13 @@ struct DirBasis {
     ~DirBasis();
 };
 
-// Device-resident cache of eigenbases keyed by (device, faces, BC, location).
-std::shared_ptr<DirBasis> basis_cache_get(int ncells, const double* faces, int bc_lo, int bc_hi, int loc,
-                                          bool host_only, std::string& err);
+// The form of a direction of a plan (host-only plans: dense).  XformKind of
+// its fast transform in fast, -1 = none.
+BasisForm basis_form(const Op1D& op, int precision, bool ylines, int nx, bool no_fast, bool need_dense, int* fast);
+// Device-resident cache of eigenbases keyed by (device, faces, BC, location,
+// form); the host eigen data is shared by the forms.
+std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, bool host_only,
+                                          std::string& err);
 size_t basis_cache_bytes();   // device bytes held by live cached bases
 
 // ---- plans ------------------------------------------------------------------
@@ -123,6 +144,10 @@ GemmDesc stage_gemm(const tpt_plan_s* p, int stage, int prec, const void* in, in
                     int epi, double* partials, int nrhs);
 // Stages of a direction with a fast transform: all lines of that direction.
 bool stage_is_fast(const tpt_plan_s* p, int stage);
+// Stages of a direction whose mirror symmetry splits its basis (fold_impl.h).
+bool stage_is_fold(const tpt_plan_s* p, int stage);
+FoldDesc stage_fold(const tpt_plan_s* p, int stage, const void* in, int tin, void* out, int tout, int epi,
+                    double* partials, int nrhs);
 FftDesc stage_fft(const tpt_plan_s* p, int stage, const void* in, int tin, void* out, int tout, int epi,
                   double* partials, int nrhs);
 ThomasDesc plan_thomas(const tpt_plan_s* p, const void* f, int tf, void* x, int tx, double* scratch, int nrhs);

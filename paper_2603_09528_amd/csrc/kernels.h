@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <vector>
 
 namespace tpt {
 
@@ -103,6 +104,55 @@ hipError_t launch_gemm_f32(const GemmDesc& g, const GemmDesc* d_work, int nwork,
                            hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmDesc& g, const GemmDesc* d_work, int nwork, long long blocks, int variant,
                             hipStream_t s);
+
+// Transform of one mirror-symmetric direction by two half-size products (see
+// fold_impl.h): every line of the direction, x lines contiguous, y lines the
+// columns of each z slab (column c = slab * inner + i).  P holds the padded
+// even and odd bases, [2][hp][kp] of the compute type; the modes of a line
+// are kept even ones first.  X and rot: the remainders and rotations of a
+// basis that is symmetric only up to rounding (FP64), or null.
+struct FoldDesc {
+    const void* P;
+    const uint16_t* X;
+    const double2* rot;
+    const void* in;
+    void* out;
+    int n, h;               // line length and (n + 1) / 2
+    int hp, kp;             // h rounded up to FOLD_ROWS and FOLD_COLS
+    int ylines, inverse;
+    int inner;              // y lines: Nx
+    long long lines;        // x: Ny Nz nrhs; y: Nx Nz nrhs
+    int tin, tout;          // DType of in / out
+    int epi;                // EPI_STORE, or EPI_ACCUM_F64 (inverse x lines, FP64 out)
+    double* partials;       // EPI_ACCUM_F64: 2 doubles per tile
+    int tiles_p;            // tiles along the modes (fold_tiles sets it)
+    long long block_begin;  // multi-problem
+};
+enum { FOLD_ROWS = 64, FOLD_COLS = 16, FOLD_MIN_N = 16, FOLD_COARSE = 32 };
+constexpr double FOLD_XSCALE = 16777216.0;  // of the remainders (2^24)
+// Tile shapes: slots x lines (64 x 64 instead of 64 x 128 with remainders).
+enum FoldShape { FOLD_64x128 = 0, FOLD_32x128 = 1, FOLD_16x64 = 2, FOLD_NSHAPE = 3 };
+// Whether a direction of n unknowns of an nx x ny plane (ylines: n = ny) fits
+// the kernel's 32-bit offsets.
+bool fold_fits(int n, int nx, bool ylines);
+// Tile shape of one launch over `count` problems (all with remainders, or none;
+// every shape gives the same bits).
+int fold_shape(const FoldDesc* g, int count);
+long long fold_tiles(FoldDesc& g, int shape);       // sets tiles_p; the tile count
+// Blocks of a launch of `total` tiles: at most what the GPU holds at once (two
+// blocks of eight waves, three of four, five of the small tile per CU).
+long long fold_grid(int shape, bool corr, long long total);
+struct FoldList {           // device arrays of a launch over several problems
+    const FoldDesc* work;   // block_begin and tiles_p set
+    int nwork;
+    const unsigned* coarse; // the problem of tiles 0, FOLD_COARSE, 2 FOLD_COARSE, ..
+};
+std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long total);
+hipError_t launch_fold(FoldDesc g, int prec, hipStream_t s);
+hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int prec, int shape,
+                             hipStream_t s);
+hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
+hipError_t launch_fold_f32(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 
 // Fast transforms of the lines of a uniform direction (analytic bases:
 // real Fourier for periodic, DCT-II for Neumann-Neumann, DST-II for

@@ -155,6 +155,41 @@ int MultiExec::add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& 
     return TPT_OK;
 }
 
+int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const std::vector<char>& use,
+                              std::vector<long long>* nb) {
+    // one persistent launch for the problems with remainders and one for the
+    // others; every tile shape gives the same bits, so batch and single results
+    // agree whatever shapes they take
+    for (int corr = 0; corr < 2; ++corr) {
+        std::vector<FoldDesc> grp;
+        std::vector<size_t> idx;
+        for (size_t i = 0; i < gs.size(); ++i) {
+            if (!use[i] || (gs[i].X != nullptr) != (corr == 1)) continue;
+            grp.push_back(gs[i]);
+            idx.push_back(i);
+        }
+        if (grp.empty()) continue;
+        const int shape = fold_shape(grp.data(), (int)grp.size());
+        long long total = 0;
+        for (size_t k = 0; k < grp.size(); ++k) {
+            const long long t = fold_tiles(grp[k], shape);
+            grp[k].block_begin = total;
+            total += t;
+            if (nb) (*nb)[idx[k]] = t;
+        }
+        Launch L{};
+        L.kind = 10;
+        L.prec = prec;
+        L.variant = shape;
+        L.off = append(blob_, grp);
+        L.off2 = append(blob_, fold_coarse(grp, total));
+        L.nwork = (int)grp.size();
+        L.total = total;
+        seq_.push_back(L);
+    }
+    return TPT_OK;
+}
+
 int MultiExec::add_fft_stage(const std::vector<FftDesc>& fs, const std::vector<char>& use) {
     // one persistent launch per line length (block shape and LDS depend on it)
     std::vector<int> lens;
@@ -201,17 +236,19 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
     auto applies = [&](int i, int stage) {
         return (stage == ST_XF || stage == ST_XI) ? plans_[i]->tx : plans_[i]->ty;
     };
-    auto fast_mask = [&](int stage, bool fast) {
+    auto form_mask = [&](int stage, int form) {
         std::vector<char> m(n);
-        for (int i = 0; i < n; ++i) m[i] = applies(i, stage) && stage_is_fast(plans_[i], stage) == fast ? 1 : 0;
+        for (int i = 0; i < n; ++i)
+            m[i] = applies(i, stage) && ((stage == ST_XF || stage == ST_XI) ? plans_[i]->bx : plans_[i]->by)->form == form;
         return m;
     };
     // one transform stage of every problem that applies it: GEMM launches
-    // grouped by tile variant, fast-transform launches grouped by line length
+    // grouped by tile variant, one launch of half-size products, fast-transform launches grouped by line length
     auto stage = [&](int st, const std::vector<const void*>& in, int tin, const std::vector<void*>& outp, int tout,
                      int epi, std::vector<long long>* nb, bool with_check = false) {
         std::vector<GemmDesc> g(n);
         std::vector<FftDesc> f(n);
+        std::vector<FoldDesc> h(n);
         for (int i = 0; i < n; ++i) {
             if (!applies(i, st)) continue;
             double* part = epi == EPI_ACCUM_F64 ? w[i].partials : nullptr;
@@ -219,12 +256,15 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
                 f[i] = stage_fft(plans_[i], st, in[i], tin, outp[i], tout, epi, part, 1);
                 if (with_check && fused[i]) attach_check(plans_[i], chk[i], f[i]);
                 if (nb) (*nb)[i] = fft_blocks(f[i]);
+            } else if (stage_is_fold(plans_[i], st)) {
+                h[i] = stage_fold(plans_[i], st, in[i], tin, outp[i], tout, epi, part, 1);
             } else {
                 g[i] = stage_gemm(plans_[i], st, prec_, in[i], tin, outp[i], tout, epi, part, 1);
             }
         }
-        add_gemm_stage(st, prec_, g, fast_mask(st, false), nb);
-        add_fft_stage(f, fast_mask(st, true));
+        add_gemm_stage(st, prec_, g, form_mask(st, BF_DENSE), nb);
+        add_fold_stage(prec_, h, form_mask(st, BF_FOLD), nb);
+        add_fft_stage(f, form_mask(st, BF_FAST));
     };
     std::vector<void*> w1(n), w2(n), outv(n);
     std::vector<const void*> w1c(n), w2c(n), rhsv(n), resv(n);
@@ -396,6 +436,13 @@ int MultiExec::enqueue(hipStream_t s) const {
                 // one large problem on its own (its single-solve tile)
                 TimedScope ts("multi_gemm", s);
                 e = launch_gemm(*(const GemmDesc*)(blob_.data() + L.off), L.prec, L.variant, s);
+                break;
+            }
+            case 10: {
+                TimedScope ts("multi_gemm", s);
+                const FoldDesc& rep = *(const FoldDesc*)(blob_.data() + L.off);
+                const FoldList list{(const FoldDesc*)(d_desc_ + L.off), L.nwork, (const unsigned*)(d_desc_ + L.off2)};
+                e = launch_fold_multi(rep, list, L.total, L.prec, L.variant, s);
                 break;
             }
             case 8: {
@@ -629,7 +676,7 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
         // word 0x3FF80000, i.e. 1.9375 in FP32 and about 1.5 in FP64
         (void)hipMemsetD32Async((hipDeviceptr_t)in, 0x3FF80000u, bytes / 4, s);
         for (int stage : {ST_XF, ST_YF}) {
-            if (stage_is_fast(p, stage)) continue;  // no GEMM in this pass
+            if (stage_is_fast(p, stage) || stage_is_fold(p, stage)) continue;  // no GEMM in this pass
             if (stage == ST_XF ? !p->tx : !p->ty) continue;  // explicit direction
             const int dt = prec == GP_F64 ? DT_F64 : DT_F32;
             GemmDesc g = stage_gemm(p, stage, prec, in, dt, outb, dt, EPI_STORE, nullptr, 1);

@@ -38,11 +38,13 @@ class MultiExec {
         int kind;     // 0 gemm, 1 sequential Thomas, 2 residual, 3 reduce, 4 x-line FFT, 5 partitioned Thomas,
                       // 6 right-hand-side check, 7 folding of fused-check partials,
                       // 8 work-list GEMM (persistent, all problems of the stage),
-                      // 9 one GEMM problem on its own (single-problem kernel)
+                      // 9 one GEMM problem on its own (single-problem kernel),
+                      // 10 half-size products of mirror directions (variant: tile shape)
         // sequential Thomas: variant holds the largest nz; partitioned: the
         // configuration, prec the storage type
         int prec, variant, b_nk;
         size_t off;   // byte offset of the first descriptor in the blob
+        size_t off2;  // half-size products: byte offset of the problems of the tiles (FoldList)
         int nwork;
         long long total;
     };
@@ -50,6 +52,8 @@ class MultiExec {
     // launch runs (the norm partials an accumulating stage writes)
     int add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& g, const std::vector<char>& use,
                        std::vector<long long>* nb = nullptr);
+    int add_fold_stage(int prec, const std::vector<FoldDesc>& g, const std::vector<char>& use,
+                       std::vector<long long>* nb);
     int add_fft_stage(const std::vector<FftDesc>& f, const std::vector<char>& use);
     std::vector<tpt_plan_s*> plans_;
     int prec_ = GP_F64;

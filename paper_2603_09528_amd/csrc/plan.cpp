@@ -46,19 +46,32 @@ DirBasis::~DirBasis() {
 // ---- eigenbasis cache ---------------------------------------------------------
 static std::mutex g_cache_mu;
 static std::map<std::string, std::weak_ptr<DirBasis>> g_cache;
+static std::map<std::string, std::weak_ptr<const Eig1D>> g_eig_cache;
 
-static std::string cache_key(int device, int ncells, const double* faces, int bc_lo, int bc_hi, int loc,
-                             bool host_only) {
+BasisForm basis_form(const Op1D& op, int precision, bool ylines, int nx, bool no_fast, bool need_dense, int* fast) {
+    *fast = -1;
+    if (!no_fast && op.uniform && fft_supported(op.n)) {
+        if (op.periodic) *fast = UT_FOURIER;
+        else if (op.loc == LOC_C && op.bc_lo == BC_N && op.bc_hi == BC_N) *fast = UT_DCT;
+        else if (op.loc == LOC_C && op.bc_lo == BC_D && op.bc_hi == BC_D) *fast = UT_DST;
+        if (*fast >= 0) return BF_FAST;
+    }
+    // the split-BF16 products read whole bases
+    if (op.mirror && !need_dense && precision != TPT_MIXED_BF16X3 && fold_fits(op.n, nx, ylines)) return BF_FOLD;
+    return BF_DENSE;
+}
+
+static std::string eig_key(const Op1D& op, int ncells, const double* faces) {
     std::string k;
     k.reserve(32 + 8 * (ncells + 1));
-    int hdr[6] = {device, ncells, bc_lo, bc_hi, loc, host_only ? 1 : 0};
+    int hdr[4] = {ncells, op.bc_lo, op.bc_hi, op.loc};
     k.append((const char*)hdr, sizeof(hdr));
     k.append((const char*)faces, sizeof(double) * (ncells + 1));
     return k;
 }
 
-std::shared_ptr<DirBasis> basis_cache_get(int ncells, const double* faces, int bc_lo, int bc_hi, int loc,
-                                          bool host_only, std::string& err) {
+std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, bool host_only,
+                                          std::string& err) {
     int device = 0;
     if (!host_only) {
         if (hipGetDevice(&device) != hipSuccess) {
@@ -66,67 +79,80 @@ std::shared_ptr<DirBasis> basis_cache_get(int ncells, const double* faces, int b
             return nullptr;
         }
     }
-    const std::string key = cache_key(device, ncells, faces, bc_lo, bc_hi, loc, host_only);
+    const std::string ekey = eig_key(op, ncells, faces);
+    int hdr[3] = {device, host_only ? 1 : 0, form};
+    const std::string key = std::string((const char*)hdr, sizeof(hdr)) + ekey;
     std::lock_guard<std::mutex> lock(g_cache_mu);
     auto it = g_cache.find(key);
     if (it != g_cache.end()) {
         if (auto sp = it->second.lock()) return sp;
     }
-    Op1D op;
-    err = build_op1d(ncells, faces, bc_lo, bc_hi, loc, op);
-    if (!err.empty()) return nullptr;
     auto b = std::make_shared<DirBasis>();
     b->device = device;
     b->n = op.n;
-    err = eig_op1d(op, b->eig);
-    if (!err.empty()) return nullptr;
+    b->form = form;
+    auto ie = g_eig_cache.find(ekey);
+    if (ie != g_eig_cache.end()) b->eig = ie->second.lock();
+    if (!b->eig) {
+        auto e = std::make_shared<Eig1D>();
+        err = eig_op1d(op, *e);
+        if (!err.empty()) return nullptr;
+        b->eig = e;
+        g_eig_cache[ekey] = b->eig;
+    }
+    const Eig1D& eig = *b->eig;
+    // an eigenbasis that does not split after all takes the dense product
+    const int h = (op.n + 1) / 2;
+    const int hp = (h + FOLD_ROWS - 1) / FOLD_ROWS * FOLD_ROWS, kp = (h + FOLD_COLS - 1) / FOLD_COLS * FOLD_COLS;
+    FoldBasis fb;
+    if (form == BF_FOLD && !fold_basis(op, eig, hp, kp, fb)) b->form = form = BF_DENSE;
+    b->null_pos = form == BF_FOLD && eig.null_index >= 0 ? eig.null_index / 2 : eig.null_index;
     if (!host_only) {
         const int n = op.n;
         const size_t nn = (size_t)n * n;
-        auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-        const size_t o_lam = 0;
-        const size_t o_qinv = o_lam + al(8 * (size_t)n);
-        const size_t o_q = o_qinv + al(8 * nn);
-        const size_t o_sqinv = o_q + al(8 * nn);
-        const size_t o_sq = o_sqinv + al(4 * nn);
+        size_t total = 0;
+        auto take = [&](size_t bytes) {
+            const size_t o = total;
+            total += (bytes + 255) & ~(size_t)255;
+            return o;
+        };
+        const size_t o_lam = take(8 * (size_t)n);
+        size_t o_qinv = 0, o_q = 0, o_sqinv = 0, o_sq = 0, o_hqinv = 0, o_lqinv = 0, o_hq = 0, o_lq = 0;
+        size_t o_tw = 0, o_qtw = 0;
         // bf16 planes: rows padded to a multiple of 8 elements (16 bytes), so
         // the split-BF16 tiles load them as vectors whatever n is
         const int ldp = (n + 7) / 8 * 8;
-        const size_t np = (size_t)n * ldp;
-        const size_t o_hqinv = o_sq + al(4 * nn);
-        const size_t o_lqinv = o_hqinv + al(2 * np);
-        const size_t o_hq = o_lqinv + al(2 * np);
-        const size_t o_lq = o_hq + al(2 * np);
-        int fk = -1;
-        if (b->eig.analytic && fft_supported(n)) {
-            if (op.periodic) fk = UT_FOURIER;
-            else if (op.loc == LOC_C && op.bc_lo == BC_N && op.bc_hi == BC_N) fk = UT_DCT;
-            else if (op.loc == LOC_C && op.bc_lo == BC_D && op.bc_hi == BC_D) fk = UT_DST;
+        const size_t nf = 2 * (size_t)hp * kp;
+        size_t o_xqinv = 0, o_xq = 0, o_rot = 0;
+        if (form == BF_FAST) {
+            o_tw = take(16 * (size_t)(n / 2));
+            o_qtw = take(16 * (size_t)(n / 2 + 1));
+        } else if (form == BF_FOLD) {
+            o_qinv = take(8 * nf);
+            o_q = take(8 * nf);
+            o_sqinv = take(4 * nf);
+            o_sq = take(4 * nf);
+            if (fb.rotated) {
+                o_xqinv = take(2 * nf);
+                o_xq = take(2 * nf);
+                o_rot = take(8 * fb.rot.size());
+            }
+        } else {
+            const size_t np = (size_t)n * ldp;
+            o_qinv = take(8 * nn);
+            o_q = take(8 * nn);
+            o_sqinv = take(4 * nn);
+            o_sq = take(4 * nn);
+            o_hqinv = take(2 * np);
+            o_lqinv = take(2 * np);
+            o_hq = take(2 * np);
+            o_lq = take(2 * np);
         }
-        const bool fft = fk >= 0;
-        const size_t o_tw = o_lq + al(2 * np);
-        const size_t o_qtw = o_tw + (fft ? al(16 * (size_t)(n / 2)) : 0);
-        const size_t total = o_qtw + (fft ? al(16 * (size_t)(n / 2 + 1)) : 0);
         std::vector<char> host(total, 0);
         double* lam = (double*)(host.data() + o_lam);
-        double* qinv = (double*)(host.data() + o_qinv);
-        double* q = (double*)(host.data() + o_q);
-        float* sqinv = (float*)(host.data() + o_sqinv);
-        float* sq = (float*)(host.data() + o_sq);
-        uint16_t* hqinv = (uint16_t*)(host.data() + o_hqinv);
-        uint16_t* lqinv = (uint16_t*)(host.data() + o_lqinv);
-        uint16_t* hq = (uint16_t*)(host.data() + o_hq);
-        uint16_t* lq = (uint16_t*)(host.data() + o_lq);
-        for (int p = 0; p < n; ++p) lam[p] = b->eig.lam[p];
-        for (int i = 0; i < n; ++i) {
-            const double si = std::sqrt(op.vol[i]);
-            for (int p = 0; p < n; ++p) {
-                const double qt = b->eig.Qt[(size_t)i * n + p];
-                qinv[(size_t)p * n + i] = qt * si;  // Q^{-1} = Q~^T D^{1/2}
-                q[(size_t)i * n + p] = qt / si;     // Q = D^{-1/2} Q~
-            }
-        }
-        if (fft) {
+        // a folded basis keeps its even modes first
+        for (int p = 0; p < n; ++p) lam[form == BF_FOLD ? p / 2 + (p & 1) * h : p] = eig.lam[p];
+        if (form == BF_FAST) {
             // twiddles of the length-n real transform and the quarter-wave
             // factors of the cosine / sine transforms, in long double
             double* tw = (double*)(host.data() + o_tw);
@@ -142,21 +168,63 @@ std::shared_ptr<DirBasis> basis_cache_get(int ncells, const double* faces, int b
                 qw[2 * k] = (double)std::cos(a);
                 qw[2 * k + 1] = (double)-std::sin(a);
             }
+        } else if (form == BF_FOLD) {
+            // by K step: [columns / w][parity][row][w], w = 64 bytes of
+            // elements with column k of the step at (k % 4, k / 4), or 16
+            // columns of the remainders in order
+            auto at = [&](size_t e, int w, bool plain = false) {
+                const size_t par = e / ((size_t)hp * kp), row = e / kp % hp, c = e % kp, k = c % w;
+                return ((c / w * 2 + par) * hp + row) * w + (plain ? k : k % 4 * (w / 4) + k / 4);
+            };
+            double* dqinv = (double*)(host.data() + o_qinv);
+            double* dq = (double*)(host.data() + o_q);
+            float* sqinv = (float*)(host.data() + o_sqinv);
+            float* sq = (float*)(host.data() + o_sq);
+            for (size_t e = 0; e < nf; ++e) {
+                dqinv[at(e, 8)] = fb.fwd[e];
+                dq[at(e, 8)] = fb.inv[e];
+                sqinv[at(e, 16)] = (float)fb.fwd[e];
+                sq[at(e, 16)] = (float)fb.inv[e];
+            }
+            if (fb.rotated) {
+                uint16_t* xi = (uint16_t*)(host.data() + o_xqinv);
+                uint16_t* xq = (uint16_t*)(host.data() + o_xq);
+                for (size_t e = 0; e < nf; ++e) {
+                    xi[at(e, 16, true)] = host_bf16((float)(fb.xfwd[e] * FOLD_XSCALE));
+                    xq[at(e, 16, true)] = host_bf16((float)(fb.xinv[e] * FOLD_XSCALE));
+                }
+                std::memcpy(host.data() + o_rot, fb.rot.data(), 8 * fb.rot.size());
+            }
+        } else {
+            double* qinv = (double*)(host.data() + o_qinv);
+            double* q = (double*)(host.data() + o_q);
+            float* sqinv = (float*)(host.data() + o_sqinv);
+            float* sq = (float*)(host.data() + o_sq);
+            uint16_t* hqinv = (uint16_t*)(host.data() + o_hqinv);
+            uint16_t* lqinv = (uint16_t*)(host.data() + o_lqinv);
+            uint16_t* hq = (uint16_t*)(host.data() + o_hq);
+            uint16_t* lq = (uint16_t*)(host.data() + o_lq);
+            for (int i = 0; i < n; ++i) {
+                const double si = std::sqrt(op.vol[i]);
+                for (int p = 0; p < n; ++p) {
+                    const double qt = eig.Qt[(size_t)i * n + p];
+                    qinv[(size_t)p * n + i] = qt * si;  // Q^{-1} = Q~^T D^{1/2}
+                    q[(size_t)i * n + p] = qt / si;     // Q = D^{-1/2} Q~
+                }
+            }
+            for (size_t e = 0; e < nn; ++e) {
+                sqinv[e] = (float)qinv[e];
+                sq[e] = (float)q[e];
+                const size_t ep = e / n * ldp + e % n;  // padded position (padding stays 0)
+                uint16_t hb = host_bf16((float)qinv[e]);
+                hqinv[ep] = hb;
+                lqinv[ep] = host_bf16((float)(qinv[e] - (double)host_bf16_to_f(hb)));
+                hb = host_bf16((float)q[e]);
+                hq[ep] = hb;
+                lq[ep] = host_bf16((float)(q[e] - (double)host_bf16_to_f(hb)));
+            }
         }
-        b->fast_kind = fk;
         b->h = op.vol[0];
-        for (size_t e = 0; e < nn; ++e) {
-            sqinv[e] = (float)qinv[e];
-            sq[e] = (float)q[e];
-            const size_t ep = e / n * ldp + e % n;  // padded position (padding stays 0)
-            uint16_t h = host_bf16((float)qinv[e]);
-            hqinv[ep] = h;
-            lqinv[ep] = host_bf16((float)(qinv[e] - (double)host_bf16_to_f(h)));
-            h = host_bf16((float)q[e]);
-            hq[ep] = h;
-            lq[ep] = host_bf16((float)(q[e] - (double)host_bf16_to_f(h)));
-        }
-        b->ldp = ldp;
         void* blk = nullptr;
         if (hipMalloc(&blk, total) != hipSuccess) {
             err = "out of device memory for an eigenbasis";
@@ -172,17 +240,31 @@ std::shared_ptr<DirBasis> basis_cache_get(int ncells, const double* faces, int b
         b->block = blk;
         b->bytes = total;
         b->d_lam = (double*)(d + o_lam);
-        b->d_qinv = (double*)(d + o_qinv);
-        b->d_q = (double*)(d + o_q);
-        b->s_qinv = (float*)(d + o_sqinv);
-        b->s_q = (float*)(d + o_sq);
-        b->h_qinv = (uint16_t*)(d + o_hqinv);
-        b->l_qinv = (uint16_t*)(d + o_lqinv);
-        b->h_q = (uint16_t*)(d + o_hq);
-        b->l_q = (uint16_t*)(d + o_lq);
-        if (fft) {
+        if (form == BF_FAST) {
             b->d_twiddle = (double2*)(d + o_tw);
             b->d_qtw = (double2*)(d + o_qtw);
+        } else if (form == BF_FOLD) {
+            b->hp = hp;
+            b->kp = kp;
+            b->fd_qinv = (double*)(d + o_qinv);
+            b->fd_q = (double*)(d + o_q);
+            b->fs_qinv = (float*)(d + o_sqinv);
+            b->fs_q = (float*)(d + o_sq);
+            if (fb.rotated) {
+                b->fx_qinv = (uint16_t*)(d + o_xqinv);
+                b->fx_q = (uint16_t*)(d + o_xq);
+                b->f_rot = (double2*)(d + o_rot);
+            }
+        } else {
+            b->ldp = ldp;
+            b->d_qinv = (double*)(d + o_qinv);
+            b->d_q = (double*)(d + o_q);
+            b->s_qinv = (float*)(d + o_sqinv);
+            b->s_q = (float*)(d + o_sq);
+            b->h_qinv = (uint16_t*)(d + o_hqinv);
+            b->l_qinv = (uint16_t*)(d + o_lqinv);
+            b->h_q = (uint16_t*)(d + o_hq);
+            b->l_q = (uint16_t*)(d + o_lq);
         }
     }
     g_cache[key] = b;
@@ -309,12 +391,19 @@ int tpt_plan_create(const tpt_plan_desc* desc, tpt_plan* out) {
         p->N[d] = p->op[d].n;
     }
     p->dof = (long long)p->N[0] * p->N[1] * p->N[2];
+    // one pass for the x transform and the y GEMM (FP64; x rows of 128 or
+    // 256 points, whole 128-row tiles of y) reads whole y bases
+    bool want_fuse = !p->host_only && p->tx && p->ty && desc->precision == TPT_FP64 && (desc->flags & TPT_FLAG_FUSE_XY) &&
+                     (p->N[0] == 128 || p->N[0] == 256) && p->N[1] % 128 == 0;
+    int fast[2] = {-1, -1}, form[2] = {BF_DENSE, BF_DENSE};
+    for (int d = 0; d < 2 && !p->host_only; ++d)
+        form[d] = basis_form(p->op[d], desc->precision, d == 1, p->N[0],
+                             (desc->flags & (d == 0 ? TPT_FLAG_DENSE_X : TPT_FLAG_DENSE_Y)) != 0,
+                             d == 1 && want_fuse && fast[0] >= 0, &fast[d]);
     std::string err;
-    p->bx = basis_cache_get(desc->n[0], p->faces[0].data(), desc->bc[0][0], desc->bc[0][1], desc->loc[0],
-                            p->host_only, err);
+    p->bx = basis_cache_get(p->op[0], desc->n[0], p->faces[0].data(), form[0], p->host_only, err);
     if (!p->bx) return fail(err.find("memory") != std::string::npos ? TPT_ERR_OOM : TPT_ERR_INVALID, "x basis: " + err);
-    p->by = basis_cache_get(desc->n[1], p->faces[1].data(), desc->bc[1][0], desc->bc[1][1], desc->loc[1],
-                            p->host_only, err);
+    p->by = basis_cache_get(p->op[1], desc->n[1], p->faces[1].data(), form[1], p->host_only, err);
     if (!p->by) return fail(err.find("memory") != std::string::npos ? TPT_ERR_OOM : TPT_ERR_INVALID, "y basis: " + err);
     if (desc->kind == TPT_POISSON) {
         p->sigma = 0.0;
@@ -324,9 +413,8 @@ int tpt_plan_create(const tpt_plan_desc* desc, tpt_plan* out) {
         p->tau = -desc->alpha;
     }
     // the null line: lambda_x = lambda_y = 0 (both exact) and a singular T_z
-    if (desc->kind == TPT_POISSON && p->bx->eig.null_index >= 0 && p->by->eig.null_index >= 0 &&
-        p->op[2].null_mode)
-        p->null_line = p->bx->eig.null_index + p->N[0] * p->by->eig.null_index;
+    if (desc->kind == TPT_POISSON && p->bx->null_pos >= 0 && p->by->null_pos >= 0 && p->op[2].null_mode)
+        p->null_line = p->bx->null_pos + p->N[0] * p->by->null_pos;
     p->info.null_line = p->null_line;
     p->run_check = p->check || (desc->precision != TPT_FP64 && p->null_line >= 0);
     {
@@ -335,14 +423,9 @@ int tpt_plan_create(const tpt_plan_desc* desc, tpt_plan* out) {
         for (double v : p->op[1].vol) ay += v;
         p->last_area_inv = 1.0 / (ax * ay * p->op[2].vol[p->N[2] - 1]);
     }
-    if (!p->host_only) {
-        if (p->bx->fast_kind >= 0 && !(desc->flags & TPT_FLAG_DENSE_X)) p->fast[0] = p->bx->fast_kind;
-        if (p->by->fast_kind >= 0 && !(desc->flags & TPT_FLAG_DENSE_Y)) p->fast[1] = p->by->fast_kind;
-        // one pass for the x transform and the y GEMM (FP64; x rows of 128 or
-        // 256 points, whole 128-row tiles of y)
-        p->fuse_xy = p->tx && p->ty && desc->precision == TPT_FP64 && (desc->flags & TPT_FLAG_FUSE_XY) && p->fast[0] >= 0 &&
-                     p->fast[1] < 0 && (p->N[0] == 128 || p->N[0] == 256) && p->N[1] % 128 == 0;
-    }
+    p->fast[0] = fast[0];
+    p->fast[1] = fast[1];
+    p->fuse_xy = want_fuse && p->fast[0] >= 0 && p->fast[1] < 0;
     p->info.rel_residual = -1.0;
     p->info.compat_defect = p->check ? 0.0 : -1.0;
     p->info.nonfinite = p->check ? 0 : -1;
@@ -418,7 +501,7 @@ int tpt_plan_workspace_bytes(tpt_plan p, size_t* bytes) {
 
 int tpt_plan_eigen(tpt_plan p, int dir, double* lam, double* Qt) {
     if (!p || !lam || dir < 0 || dir > 1) return fail(TPT_ERR_INVALID, "bad argument");
-    const Eig1D& e = (dir == 0 ? p->bx : p->by)->eig;
+    const Eig1D& e = *(dir == 0 ? p->bx : p->by)->eig;
     std::memcpy(lam, e.lam.data(), sizeof(double) * e.n);
     if (Qt) std::memcpy(Qt, e.Qt.data(), sizeof(double) * (size_t)e.n * e.n);
     return TPT_OK;

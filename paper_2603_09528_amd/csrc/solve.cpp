@@ -199,6 +199,37 @@ bool stage_is_fast(const tpt_plan_s* p, int stage) {
     return p->fast[(stage == ST_XF || stage == ST_XI) ? 0 : 1] >= 0;
 }
 
+bool stage_is_fold(const tpt_plan_s* p, int stage) {
+    return ((stage == ST_XF || stage == ST_XI) ? p->bx : p->by)->form == BF_FOLD;
+}
+
+FoldDesc stage_fold(const tpt_plan_s* p, int stage, const void* in, int tin, void* out, int tout, int epi,
+                    double* partials, int nrhs) {
+    const bool xdir = stage == ST_XF || stage == ST_XI, fwd = stage == ST_XF || stage == ST_YF;
+    const DirBasis* b = xdir ? p->bx.get() : p->by.get();
+    FoldDesc g{};
+    if (plan_gemm_prec(p) == GP_F64) {
+        g.P = fwd ? b->fd_qinv : b->fd_q;
+        g.X = fwd ? b->fx_qinv : b->fx_q;
+        g.rot = b->f_rot;
+    } else g.P = fwd ? b->fs_qinv : b->fs_q;
+    g.in = in;
+    g.out = out;
+    g.n = xdir ? p->N[0] : p->N[1];
+    g.h = (g.n + 1) / 2;
+    g.hp = b->hp;
+    g.kp = b->kp;
+    g.ylines = xdir ? 0 : 1;
+    g.inverse = fwd ? 0 : 1;
+    g.inner = p->N[0];
+    g.lines = (long long)(xdir ? p->N[1] : p->N[0]) * p->N[2] * nrhs;
+    g.tin = tin;
+    g.tout = tout;
+    g.epi = epi;
+    g.partials = partials;
+    return g;
+}
+
 FftDesc stage_fft(const tpt_plan_s* p, int stage, const void* in, int tin, void* out, int tout, int epi,
                   double* partials, int nrhs) {
     const bool xdir = stage == ST_XF || stage == ST_XI;
@@ -333,11 +364,20 @@ static const char* fast_name(int stage, int tin, int tout) {
 }
 
 // One transform stage: the fast transform where the plan uses one for that
-// direction, else the GEMM.  chk (x forward by fast transform only): the
+// direction, two half-size products where the direction is mirror-symmetric,
+// else the GEMM.  chk (x forward by fast transform only): the
 // right-hand-side check fused into its loads.
 static int run_stage(const tpt_plan_s* p, int stage, int prec, const void* in, int tin, void* out, int tout,
                      int epi, double* partials, int nrhs, hipStream_t s, long long* nblocks = nullptr,
                      const CheckDesc* chk = nullptr) {
+    if (stage_is_fold(p, stage)) {
+        FoldDesc g = stage_fold(p, stage, in, tin, out, tout, epi, partials, nrhs);
+        if (nblocks) *nblocks = fold_tiles(g, fold_shape(&g, 1));
+        TimedScope ts(stage_name(stage, prec), s);
+        hipError_t e = launch_fold(g, prec, s);
+        if (e != hipSuccess) return fail(TPT_ERR_HIP, std::string("transform launch: ") + hipGetErrorString(e));
+        return TPT_OK;
+    }
     if (!stage_is_fast(p, stage)) return run_gemm(p, stage, prec, in, tin, out, tout, epi, partials, nrhs, s, nblocks);
     FftDesc f = stage_fft(p, stage, in, tin, out, tout, epi, partials, nrhs);
     if (chk) attach_check(p, *chk, f);
