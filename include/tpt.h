@@ -95,8 +95,7 @@ enum {
                                behind its MFMAs), so it is not the default */
     TPT_FLAG_SEQ_THOMAS = 16, /* solve the z lines with the sequential kernel
                                (one lane per line) instead of the partitioned
-                               one (segments joined by an interface system);
-                               periodic z always uses the sequential kernel */
+                               one (segments joined by an interface system) */
     TPT_FLAG_NO_CHECK = 32  /* skip the right-hand-side check of every solve
                                (one extra read of rhs on the device); the
                                compat_defect and nonfinite fields of tpt_info
@@ -384,8 +383,8 @@ int tpt_server_destroy(tpt_server server);
  * 4 * nx * ny * nsys * ceil(nz / 16) elements (chunk checkpoints).
  * pin_line >= 0 sets the last unknown of that line to zero and drops its
  * last equation (§3 gauge).  f may equal x.
- * variant: -1 automatic (what plans use); 0 sequential (one lane per line,
- * the only kernel for cyclic lines); 1..17 partitioned (each line cut into
+ * variant: -1 automatic (what plans use; partitioned from 16 planes on, plain
+ * and cyclic); 0 sequential (one lane per line); 1..17 partitioned (each line cut into
  * P segments of L planes solved in parallel and joined by a P-row interface
  * system, LB lines per block), (LB, P, L) = (64,4,8) (64,8,8) (32,8,8)
  * (64,8,16) (32,8,16) (16,8,16) (64,16,16) (32,16,16) (16,16,16) (64,8,32)

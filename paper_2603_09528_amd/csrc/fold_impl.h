@@ -72,8 +72,8 @@ template <int PH, int DN, int WP, int WD> struct FoldCfg {
     static constexpr int WAVES_P = PH / WP, WAVES_D = DN / WD;
     static constexpr int NT = 64 * WAVES_P * WAVES_D;
     static constexpr int MP = WP / 16, MD = WD / 16;
-    // waves per SIMD: two blocks of eight waves, three or five of four
-    static constexpr int WPE = NT == 512 ? 4 : PH == 32 ? 3 : 5;
+    // waves per SIMD: two blocks of eight waves, three of four, or four and more
+    static constexpr int WPE = PH == 32 && NT == 256 ? 3 : 4;
 };
 
 struct FoldTile {

@@ -484,7 +484,7 @@ hipError_t launch_thomas(const ThomasDesc& t, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int variant = thomas_variant(t);
     if (variant < 0) return hipErrorInvalidValue;
-    if (variant >= THOMAS_PART) return launch_thomas_part(t, variant - THOMAS_PART, s);
+    if (variant >= THOMAS_PART) return launch_thomas_part(t, thomas_config(variant), s);
     const long long blocks = thomas_blocks(t);
     const dim3 gr((unsigned)blocks), bl(THOMAS_NT);
     const size_t sm = THOMAS_LDS_PLANES * sizeof(double) * (size_t)t.nz;

@@ -320,7 +320,7 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
                 if (var[i] != v) continue;
                 ThomasDesc d = all[i];
                 d.block_begin = blocks;
-                blocks += v == THOMAS_SEQ ? thomas_blocks(d) : thomas_part_blocks(d, v - THOMAS_PART);
+                blocks += v == THOMAS_SEQ ? thomas_blocks(d) : thomas_part_blocks(d, thomas_config(v));
                 nz_max = std::max(nz_max, d.nz);
                 t.push_back(d);
             }
@@ -329,7 +329,8 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
             L.off = append(blob_, t);
             L.nwork = (int)t.size();
             L.total = blocks;
-            L.variant = v == THOMAS_SEQ ? nz_max : v - THOMAS_PART;
+            L.variant = v == THOMAS_SEQ ? nz_max : thomas_config(v);
+            L.b_nk = v >= THOMAS_CYC ? 1 : 0;
             L.prec = tmid;
             seq_.push_back(L);
         }
@@ -478,7 +479,7 @@ int MultiExec::enqueue(hipStream_t s) const {
             case 5: {
                 TimedScope ts("multi_thomas", s);
                 e = launch_thomas_part_multi((const ThomasDesc*)(d_desc_ + L.off), L.nwork, L.total, L.variant,
-                                             L.prec, s);
+                                             L.b_nk != 0, L.prec, s);
                 break;
             }
             case 2: {

@@ -41,7 +41,7 @@ class MultiExec {
                       // 9 one GEMM problem on its own (single-problem kernel),
                       // 10 half-size products of mirror directions (variant: tile shape)
         // sequential Thomas: variant holds the largest nz; partitioned: the
-        // configuration, prec the storage type
+        // configuration, prec the storage type, b_nk set for cyclic lines
         int prec, variant, b_nk;
         size_t off;   // byte offset of the first descriptor in the blob
         size_t off2;  // half-size products: byte offset of the problems of the tiles (FoldList)

@@ -1,4 +1,4 @@
-// Partitioned batched Thomas along z (§2.2.2 step 2.3) for non-periodic
+// Partitioned batched Thomas along z (§2.2.2 step 2.3), plain and cyclic
 // lines: single- and multi-problem launches over a table of (lines per
 // block, segments, planes per segment) configurations.
 #include "device_common.h"
@@ -10,7 +10,7 @@
 namespace tpt {
 
 // ---------------------------------------------------------------------------
-// Partitioned Thomas (non-periodic lines): each line is split into P
+// Partitioned Thomas: each line is split into P
 // segments of L planes, one lane per (line, segment), LB lines per block
 // (lane t holds segment t / LB of line t % LB, so every load and store of a
 // plane touches LB consecutive lines).  The segment's planes stay in
@@ -39,6 +39,17 @@ namespace tpt {
 // f = 0: x_{nz-1} = 0 and rows 0..nz-2 unchanged, the gauge of §3.  Without
 // pivoting the elimination relies, as the sequential one does, on the
 // diagonal dominance of D + tau lambda.
+//
+// Cyclic lines (CYC, periodic z): the interface system closes on itself
+// (z_{-1} = z_{P-1}), and parallel cyclic reduction runs on it as it is, with
+// neighbours modulo P: at the last level both are the same row, so the two
+// couplings it leaves fall on the row itself.  A line must end with its last
+// segment then: the rows are dealt out evenly, nz / P or one more to a segment
+// (at most L), the interior takes the first places, the interface row stays in
+// place L-1, and places between are skipped.  The line's data is read once and
+// written once where the sequential kernel reads it three times (two
+// eliminations and the closing) along one chain per line: 256^3, FP64, 56 us
+// against 149.
 // ---------------------------------------------------------------------------
 template <int LB, int P, int L>
 struct ThomasPartLds {
@@ -52,14 +63,22 @@ struct ThomasPartLds {
 };
 
 // One block of LB lines (block index blk of the problem t with nlines lines).
-template <int LB, int P, int L, typename TF, typename TX>
+template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long nlines, long long blk,
                                                   ThomasPartLds<LB, P, L>& sh) {
     constexpr int NT = LB * P, M = L - 1, CS = L + 1, PIN = P * CS;
     constexpr int NE = (P + 1) * L, SI = (NE + NT - 1) / NT;  // staged rows, per thread
     static_assert(L >= 4, "segments need interior rows");
     const int nz = t.nz;
-    const int sp = (nz - 1) / L;  // segment of row nz-1
+    // CYC: rows of segment q are qn q + min(q, qr) .., qn + (q < qr) of them
+    const int qn = nz / P, qr = nz % P;
+    const int sp = CYC ? P - 1 : (nz - 1) / L;  // segment of row nz-1
+    // row of place r of segment q; CYC: -1 where the place is skipped
+    auto row_of = [&](int q, int r) {
+        if constexpr (!CYC) return q * L + r;
+        const int first = qn * q + min(q, qr), n = qn + (q < qr ? 1 : 0);
+        return r == M ? first + n - 1 : r < n - 1 ? first + r : -1;
+    };
 
     // Prologue, two forms.  EAGER: every global load of the block is issued
     // before any is waited for (at clamped, valid addresses, without
@@ -79,11 +98,11 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     // nz-1 as the identity
     auto stage_row = [&](int e, double a, double b, double c) {
         const int seg = e / L, r = e - seg * L;
-        const int k = (seg < P ? seg : sp) * L + r;
+        const int k = row_of(seg < P ? seg : sp, r);
         double4 v = make_double4(0.0, 0.0, 1.0, 0.0);
-        if (k < nz && !(seg == P && k == nz - 1)) {
-            v.x = k > 0 ? t.tau * a : 0.0;
-            v.y = k < nz - 1 ? t.tau * c : 0.0;
+        if (k >= 0 && k < nz && !(seg == P && k == nz - 1)) {
+            v.x = CYC || k > 0 ? t.tau * a : 0.0;
+            v.y = CYC || k < nz - 1 ? t.tau * c : 0.0;
             v.z = t.sigma + t.tau * b;
             v.w = 1.0;
         }
@@ -93,7 +112,7 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
 #pragma unroll
         for (int q = 0; q < SI; ++q) {
             const int e = threadIdx.x + q * NT, seg = e / L;
-            const int k = min((seg < P ? seg : sp) * L + (e - seg * L), nz - 1);
+            const int k = min(max(row_of(seg < P ? seg : sp, e - seg * L), 0), nz - 1);
             za[q] = t.az[k];
             zb[q] = t.bz[k];
             zc[q] = t.cz[k];
@@ -101,7 +120,7 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     } else {
         for (int e = threadIdx.x; e < NE; e += NT) {
             const int seg = e / L;
-            const int k = min((seg < P ? seg : sp) * L + (e - seg * L), nz - 1);
+            const int k = min(max(row_of(seg < P ? seg : sp, e - seg * L), 0), nz - 1);
             stage_row(e, t.az[k], t.bz[k], t.cz[k]);
         }
     }
@@ -115,7 +134,8 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     const int i = (int)(line % t.nx), j = (int)(line / t.nx);
     const double tl = t.tau * (t.lamx[i] + t.lamy[j]);
     const bool pinned = line == t.pin_line;
-    const int k0 = s * L;
+    const int k0 = CYC ? qn * s + min(s, qr) : s * L;
+    const int mi = CYC ? qn + (s < qr ? 1 : 0) - 1 : M;  // interior rows
     const long long base = (long long)sys * S * nz + line;
     const TF* f = (const TF*)t.f + base;
     TX* x = (TX*)t.x + base;
@@ -124,12 +144,17 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     double fv[L];
     if constexpr (EAGER) {
 #pragma unroll
-        for (int r = 0; r < L; ++r) fv[r] = (double)f[(long long)min(k0 + r, nz - 1) * S];
+        for (int r = 0; r < L; ++r)
+            fv[r] = (double)f[(long long)(CYC ? k0 + (r == M ? mi : min(r, mi)) : min(k0 + r, nz - 1)) * S];
 #pragma unroll
         for (int q = 0; q < SI; ++q)
             if (threadIdx.x + q * NT < NE) stage_row(threadIdx.x + q * NT, za[q], zb[q], zc[q]);
     } else {
-        if (live && full) {
+        if constexpr (CYC) {
+            // (skipped places read the interface row: no data of their own)
+#pragma unroll
+            for (int r = 0; r < L; ++r) fv[r] = (double)f[(long long)(k0 + (r == M ? mi : min(r, mi))) * S];
+        } else if (live && full) {
 #pragma unroll
             for (int r = 0; r < L; ++r) fv[r] = (double)f[(long long)(k0 + r) * S];
         } else {
@@ -139,7 +164,7 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
         if (pinned && s == sp) {
 #pragma unroll
             for (int r = 0; r < L; ++r)
-                if (k0 + r == nz - 1) fv[r] = 0.0;
+                if (CYC ? r == M : k0 + r == nz - 1) fv[r] = 0.0;
         }
     }
     __syncthreads();
@@ -159,25 +184,44 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
         double4 v = cb[0];
         ip[0] = recip(__builtin_fma(v.w, tl, v.z));
         double Fd = fv[0] * ip[0], Gd = v.x * ip[0], cprev = v.y;
+        [[maybe_unused]] double iplast = ip[0];
 #pragma unroll
         for (int r = 1; r < M; ++r) {
+            if constexpr (CYC) {
+                ip[r] = 0.0;
+                if (r >= mi) continue;
+            }
             v = cb[r];
             ip[r] = recip(__builtin_fma(v.w, tl, v.z) - v.x * cprev * ip[r - 1]);
             Fd = (fv[r] - v.x * Fd) * ip[r];
             Gd = -v.x * Gd * ip[r];
             cprev = v.y;
+            iplast = ip[r];
         }
         Ud = Fd;
-        Vd = -cprev * ip[M - 1];
+        Vd = -cprev * (CYC ? iplast : ip[M - 1]);
         Wd = -Gd;
         // re-read the coefficients rather than keep the down sweep's in
         // registers
         asm volatile("" ::: "memory");
-        v = cb[M - 1];
-        double jp = recip(__builtin_fma(v.w, tl, v.z));
-        double Fu = fv[M - 1] * jp, Hu = v.y * jp, anext = v.x;
+        double jp, Fu, Hu, anext;
+        if constexpr (CYC) {
+            // starts at the last interior row below: with nothing behind it
+            // (anext = 0), its own C as the response to the interface
+            jp = 0.0;
+            Fu = 0.0;
+            Hu = -1.0;
+            anext = 0.0;
+        } else {
+            v = cb[M - 1];
+            jp = recip(__builtin_fma(v.w, tl, v.z));
+            Fu = fv[M - 1] * jp;
+            Hu = v.y * jp;
+            anext = v.x;
+        }
 #pragma unroll
-        for (int r = M - 2; r >= 0; --r) {
+        for (int r = CYC ? M - 1 : M - 2; r >= 0; --r) {
+            if (CYC && r >= mi) continue;
             v = cb[r];
             jp = recip(__builtin_fma(v.w, tl, v.z) - v.y * anext * jp);
             Fu = (fv[r] - v.y * Fu) * jp;
@@ -212,8 +256,8 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
         rb = __builtin_fma(v.w, tl, v.z) + A * Vd;
         rc = 0.0;
         rd = fv[M] - A * Ud;
-        if (s + 1 < P) {
-            const int nb = me + LB;
+        if (CYC || s + 1 < P) {
+            const int nb = CYC && s + 1 == P ? l : me + LB;
             rb += C * sh.pcr[1][2][nb];
             rc = C * sh.pcr[1][1][nb];
             rd -= C * sh.pcr[1][0][nb];
@@ -229,20 +273,22 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
         R[3][me] = ib;
         __syncthreads();
         double na = 0.0, nc = 0.0, nb = rb, nd = rd;
-        if (s >= h) {
-            const int u = me - h * LB;
+        if (CYC || s >= h) {
+            const int u = CYC ? ((s - h) & (P - 1)) * LB + l : me - h * LB;
             const double k1 = ra * R[3][u];
             na = -R[0][u] * k1;
             nb -= R[1][u] * k1;
             nd -= R[2][u] * k1;
         }
-        if (s + h < P) {
-            const int u = me + h * LB;
+        if (CYC || s + h < P) {
+            const int u = CYC ? ((s + h) & (P - 1)) * LB + l : me + h * LB;
             const double k2 = rc * R[3][u];
             nc = -R[1][u] * k2;
             nb -= R[0][u] * k2;
             nd -= R[2][u] * k2;
         }
+        // (cyclic, last level: both couplings are to the row itself)
+        if (CYC && 2 * h == P) nb += na + nc;
         ra = na;
         rb = nb;
         rc = nc;
@@ -253,8 +299,29 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     __syncthreads();
 
     // ---- pass 2: interior Thomas with the interface values folded in ----
-    const double Xr = sh.zz[s][l], Xl = s > 0 ? sh.zz[s - 1][l] : 0.0;
+    const double Xr = sh.zz[s][l], Xl = s > 0 ? sh.zz[s - 1][l] : CYC ? sh.zz[P - 1][l] : 0.0;
     fv[0] -= cb[0].x * Xl;
+    if constexpr (CYC) {
+        if (mi == 1) fv[0] -= cb[0].y * Xr;
+        fv[0] *= ip[0];
+#pragma unroll
+        for (int r = 1; r < M; ++r) {
+            if (r >= mi) continue;
+            const double4 v = cb[r];
+            if (r + 1 == mi) fv[r] -= v.y * Xr;
+            fv[r] = (fv[r] - v.x * fv[r - 1]) * ip[r];
+        }
+#pragma unroll
+        for (int r = M - 2; r >= 0; --r)
+            if (r + 1 < mi) fv[r] -= cb[r].y * ip[r] * fv[r + 1];
+        if (live) {
+#pragma unroll
+            for (int r = 0; r < M; ++r)
+                if (r < mi) x[(long long)(k0 + r) * S] = (TX)fv[r];
+            x[(long long)(k0 + mi) * S] = (TX)Xr;
+        }
+        return;
+    }
     fv[M - 1] -= cb[M - 1].y * Xr;
     fv[0] *= ip[0];
 #pragma unroll
@@ -272,15 +339,16 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     }
 }
 
-template <int LB, int P, int L, typename TF, typename TX>
+template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __global__ __launch_bounds__(LB * P) void thomas_part_kernel(ThomasDesc t, long long nlines) {
     __shared__ ThomasPartLds<LB, P, L> sh;
-    thomas_part_block<LB, P, L, TF, TX>(t, nlines, blockIdx.x, sh);
+    thomas_part_block<LB, P, L, CYC, TF, TX>(t, nlines, blockIdx.x, sh);
 }
 
 // Multi-problem: block_begin counts blocks of LB lines per problem; every
-// problem of the list has the same storage types and P L >= nz.
-template <int LB, int P, int L, typename TF, typename TX>
+// problem of the list has the same storage types and boundary (plain or
+// cyclic) and P L >= nz.
+template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __global__ __launch_bounds__(LB * P) void thomas_part_multi_kernel(const ThomasDesc* __restrict__ work, int nwork,
                                                                    long long total_blocks) {
     __shared__ ThomasPartLds<LB, P, L> sh;
@@ -292,7 +360,7 @@ __global__ __launch_bounds__(LB * P) void thomas_part_multi_kernel(const ThomasD
             else hi = mid - 1;
         }
         const ThomasDesc t = work[lo];
-        thomas_part_block<LB, P, L, TF, TX>(t, (long long)t.nx * t.ny * t.nsys, blk - t.block_begin, sh);
+        thomas_part_block<LB, P, L, CYC, TF, TX>(t, (long long)t.nx * t.ny * t.nsys, blk - t.block_begin, sh);
         __syncthreads();
     }
 }
@@ -357,11 +425,17 @@ int thomas_variant(const ThomasDesc& t) {
     const bool same = t.tf == t.tx;
     if (t.variant == THOMAS_SEQ) return THOMAS_SEQ;
     if (t.variant == THOMAS_AUTO) {
-        if (t.periodic || !same || t.nz < 16) return THOMAS_SEQ;
+        if (!same || t.nz < 16) return THOMAS_SEQ;
         const int v = thomas_part_auto(t.nz, (long long)t.nx * t.ny * t.nsys);
-        return v < 0 ? THOMAS_SEQ : THOMAS_PART + v;
+        // cyclic lines in the same configuration; its segments have at least
+        // two rows (nz >= 2 P) by the table's choice of P
+        return v < 0 ? THOMAS_SEQ : (t.periodic ? THOMAS_CYC : THOMAS_PART) + v;
     }
-    const int v = t.variant - THOMAS_PART;
+    if (t.variant >= THOMAS_CYC && t.variant < THOMAS_CYC + THOMAS_NPART) {
+        const ThomasPart& c = THOMAS_PARTS[t.variant - THOMAS_CYC];
+        return t.periodic && same && c.P * c.L >= t.nz && t.nz >= 2 * c.P ? t.variant : -1;
+    }
+    const int v = t.variant - THOMAS_PART;  // plain lines only
     if (v < 0 || v >= THOMAS_NPART || t.periodic || !same || THOMAS_PARTS[v].P * THOMAS_PARTS[v].L < t.nz)
         return -1;
     return t.variant;
@@ -372,16 +446,31 @@ long long thomas_part_blocks(const ThomasDesc& t, int v) {
     return ((long long)t.nx * t.ny * t.nsys + lb - 1) / lb;
 }
 
+// Configurations compiled for cyclic lines: those of the automatic choice.
+#define TPT_THOMAS_CYC(X) \
+    X(64, 4, 8)           \
+    X(32, 8, 8)           \
+    X(32, 8, 16)          \
+    X(32, 16, 16)         \
+    X(16, 16, 16)         \
+    X(16, 32, 16)         \
+    X(32, 16, 32)         \
+    X(16, 64, 16)
+
 template <typename T>
 static hipError_t launch_part_t(const ThomasDesc& t, int v, hipStream_t s) {
     const long long n = (long long)t.nx * t.ny * t.nsys;
     const dim3 gr((unsigned)thomas_part_blocks(t, v));
-#define TPT_TP_CASE(XLB, XP, XL)                                                           \
-    if (THOMAS_PARTS[v].LB == XLB && THOMAS_PARTS[v].P == XP && THOMAS_PARTS[v].L == XL) { \
-        TPT_KLAUNCH((thomas_part_kernel<XLB, XP, XL, T, T>), gr, dim3(XLB * XP), 0, s, t, n); \
-        return hipGetLastError();                                                       \
+    const ThomasPart& c = THOMAS_PARTS[v];
+#define TPT_TP_CASE(CYC_, XLB, XP, XL)                                                              \
+    if (t.periodic == (CYC_ ? 1 : 0) && c.LB == XLB && c.P == XP && c.L == XL) {                    \
+        TPT_KLAUNCH((thomas_part_kernel<XLB, XP, XL, CYC_, T, T>), gr, dim3(XLB * XP), 0, s, t, n); \
+        return hipGetLastError();                                                                   \
     }
-    TPT_THOMAS_PARTS(TPT_TP_CASE)
+#define TPT_TP_PLAIN(XLB, XP, XL) TPT_TP_CASE(false, XLB, XP, XL)
+#define TPT_TP_CYC(XLB, XP, XL) TPT_TP_CASE(true, XLB, XP, XL)
+    TPT_THOMAS_PARTS(TPT_TP_PLAIN)
+    TPT_THOMAS_CYC(TPT_TP_CYC)
 #undef TPT_TP_CASE
     return hipErrorInvalidValue;
 }
@@ -392,26 +481,30 @@ hipError_t launch_thomas_part(const ThomasDesc& t, int v, hipStream_t s) {
 }
 
 template <typename T>
-static hipError_t launch_part_multi_t(const ThomasDesc* d_work, int nwork, long long total_blocks, int v,
+static hipError_t launch_part_multi_t(const ThomasDesc* d_work, int nwork, long long total_blocks, int v, bool cyc,
                                       hipStream_t s) {
     const dim3 gr((unsigned)std::min(total_blocks, 8 * PERSISTENT_BLOCKS));
-#define TPT_TP_CASE(XLB, XP, XL)                                                                          \
-    if (THOMAS_PARTS[v].LB == XLB && THOMAS_PARTS[v].P == XP && THOMAS_PARTS[v].L == XL) {                \
-        TPT_KLAUNCH((thomas_part_multi_kernel<XLB, XP, XL, T, T>), gr, dim3(XLB * XP), 0, s, d_work, nwork, \
-                    total_blocks);                                                                     \
-        return hipGetLastError();                                                                      \
+    const ThomasPart& c = THOMAS_PARTS[v];
+#define TPT_TP_CASE(CYC_, XLB, XP, XL)                                                                            \
+    if (cyc == CYC_ && c.LB == XLB && c.P == XP && c.L == XL) {                                                   \
+        TPT_KLAUNCH((thomas_part_multi_kernel<XLB, XP, XL, CYC_, T, T>), gr, dim3(XLB * XP), 0, s, d_work, nwork, \
+                    total_blocks);                                                                                \
+        return hipGetLastError();                                                                                 \
     }
-    TPT_THOMAS_PARTS(TPT_TP_CASE)
+    TPT_THOMAS_PARTS(TPT_TP_PLAIN)
+    TPT_THOMAS_CYC(TPT_TP_CYC)
 #undef TPT_TP_CASE
+#undef TPT_TP_PLAIN
+#undef TPT_TP_CYC
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_thomas_part_multi(const ThomasDesc* d_work, int nwork, long long total_blocks, int v, int dtype,
-                                    hipStream_t s) {
+hipError_t launch_thomas_part_multi(const ThomasDesc* d_work, int nwork, long long total_blocks, int v, bool cyc,
+                                    int dtype, hipStream_t s) {
     if (total_blocks <= 0) return hipSuccess;
     if (v < 0 || v >= THOMAS_NPART) return hipErrorInvalidValue;
-    return dtype == DT_F64 ? launch_part_multi_t<double>(d_work, nwork, total_blocks, v, s)
-                           : launch_part_multi_t<float>(d_work, nwork, total_blocks, v, s);
+    return dtype == DT_F64 ? launch_part_multi_t<double>(d_work, nwork, total_blocks, v, cyc, s)
+                           : launch_part_multi_t<float>(d_work, nwork, total_blocks, v, cyc, s);
 }
 
 }  // namespace tpt
