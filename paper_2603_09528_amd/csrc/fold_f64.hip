@@ -6,18 +6,20 @@
 
 namespace tpt {
 
-bool fold_fits(int n, int nx, bool ylines) {
+bool fold_fits(int n, int nx, bool ylines, int prec) {
     const long long hp = ((n + 1) / 2 + FOLD_ROWS - 1) / FOLD_ROWS * FOLD_ROWS;
-    const long long kp = ((n + 1) / 2 + FOLD_COLS - 1) / FOLD_COLS * FOLD_COLS;
+    const long long kp = ((n + 1) / 2 + fold_cols(prec) - 1) / fold_cols(prec) * fold_cols(prec);
     const long long lim = 0x7fffff00LL / 8;
-    if (n < FOLD_MIN_N || 2 * hp * kp > lim) return false;
+    // (a K step and its mirror image have to lie in the line)
+    if (n < std::max((int)FOLD_MIN_N, prec == GP_BF16X3 ? 32 : 0) || 2 * hp * kp > lim) return false;
     // a tile's lines: 128 x lines, or columns of at most 128 / nx + 2 slabs
     return ylines ? (long long)nx * n * (128 / nx + 2) <= lim : 128LL * n <= lim;
 }
 
 static void fold_dims(const FoldDesc& g, int shape, int* ph, int* dn) {
     *ph = shape == FOLD_64x128 ? 64 : shape == FOLD_32x128 ? 32 : 16;
-    *dn = shape == FOLD_16x64 || (shape == FOLD_64x128 && g.X) ? 64 : 128;
+    if (g.prec == GP_BF16X3) *dn = shape == FOLD_64x128 ? 128 : 64;
+    else *dn = shape == FOLD_16x64 || (shape == FOLD_64x128 && g.X) ? 64 : 128;
 }
 
 long long fold_tiles(FoldDesc& g, int shape) {
@@ -36,16 +38,16 @@ long long fold_tiles(FoldDesc& g, int shape) {
 // 32 x 128 against 36 in 64 x 64 (remainders) and 26 against 38 in 64 x 128;
 // 64 x 48 x 64, 6-8 us in 16 x 64 against 8 us.
 static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
-    static const double rate[2][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.92, 0.55}};
+    static const double rate[3][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.92, 0.55}, {1.0, 0.7, 0.0}};
     int ph, dn;
     fold_dims(g, shape, &ph, &dn);
-    return (double)((tiles + 255) / 256) * ph * dn / rate[g.X ? 1 : 0][shape];
+    return (double)((tiles + 255) / 256) * ph * dn / rate[g.prec == GP_BF16X3 ? 2 : g.X ? 1 : 0][shape];
 }
 
 int fold_shape(const FoldDesc* g, int count) {
     int best = 0;
     double cost = 0.0;
-    for (int v = 0; v < FOLD_NSHAPE; ++v) {
+    for (int v = 0; v < (g[0].prec == GP_BF16X3 ? 2 : (int)FOLD_NSHAPE); ++v) {
         long long tiles = 0;
         for (int i = 0; i < count; ++i) {
             FoldDesc t = g[i];
@@ -60,8 +62,9 @@ int fold_shape(const FoldDesc* g, int count) {
     return best;
 }
 
-long long fold_grid(int shape, bool corr, long long total) {
-    const long long percu = shape == FOLD_64x128 || (shape == FOLD_32x128 && corr) ? 2 : shape == FOLD_32x128 ? 3 : 5;
+long long fold_grid(const FoldDesc& g, int shape, long long total) {
+    long long percu = shape == FOLD_64x128 || (shape == FOLD_32x128 && g.X) ? 2 : shape == FOLD_32x128 ? 3 : 5;
+    if (g.prec == GP_BF16X3 && shape == FOLD_32x128) percu = 4;
     return std::min(total, 256 * percu);
 }
 
@@ -75,15 +78,20 @@ std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long tota
     return c;
 }
 
-hipError_t launch_fold(FoldDesc g, int prec, hipStream_t s) {
-    const int shape = fold_shape(&g, 1);
-    const long long total = fold_tiles(g, shape);
-    return prec == GP_F64 ? launch_fold_f64(g, nullptr, total, shape, s) : launch_fold_f32(g, nullptr, total, shape, s);
+static hipError_t launch_any(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s) {
+    return g.prec == GP_F64   ? launch_fold_f64(g, list, total, shape, s)
+           : g.prec == GP_F32 ? launch_fold_f32(g, list, total, shape, s)
+                              : launch_fold_bf16(g, list, total, shape, s);
 }
 
-hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int prec, int shape,
-                             hipStream_t s) {
-    return prec == GP_F64 ? launch_fold_f64(rep, &list, total, shape, s) : launch_fold_f32(rep, &list, total, shape, s);
+hipError_t launch_fold(FoldDesc g, hipStream_t s) {
+    const int shape = fold_shape(&g, 1);
+    const long long total = fold_tiles(g, shape);
+    return launch_any(g, nullptr, total, shape, s);
+}
+
+hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int shape, hipStream_t s) {
+    return launch_any(rep, &list, total, shape, s);
 }
 
 template <bool CORR>

@@ -133,6 +133,90 @@ __device__ __forceinline__ f4 fold_transpose(f4 v) {
     return (f4){__uint_as_float(a[0]), __uint_as_float(a[1]), __uint_as_float(a[2]), __uint_as_float(a[3])};
 }
 
+// Results of a wave: acc[0], acc[1] of slots p0 .. and lines l0 .. of the tile
+// (FP32 and FP64 MFMA results; y lines: rows of the result are slots, its
+// columns lines; x lines the other way round).  se, sx: sums of EPI_ACCUM_F64.
+template <typename TM, typename TO, int EPI, bool Y, bool INV, int MP, int MD>
+__device__ __forceinline__ void fold_store(const FoldDesc& g, const FoldTile& cur,
+                                           const typename Mfma<TM>::acc (&acc)[2][MP][MD], int p0, int l0, int lr, int lg,
+                                           double& se, double& sx) {
+    typedef Mfma<TM> MM;
+    constexpr int eo = (int)sizeof(TO);
+    const int ho = g.n - g.h;       // position of odd slot 0
+    const int odd = g.n & 1;        // slot 0 has no odd mode, row H-1 is its own mirror
+    // two results of an element: positions p and ho + p (modes), or rows p
+    // and n - 1 - p.  An offset past any buffer drops the store.
+    constexpr unsigned NOWHERE = 0xffffffffu;
+    const unsigned step = (unsigned)(Y ? g.inner : 1) * eo;   // between positions of a line
+    const unsigned lstep = (unsigned)(Y ? 1 : g.n) * eo;      // between lines of the tile (y: of a slab)
+    __amdgpu_buffer_rsrc_t rC;
+    unsigned inner = 1, b0 = 0;
+    if constexpr (Y) {
+        inner = (unsigned)g.inner;
+        b0 = cur.d0 / inner;
+        const unsigned slab = inner * (unsigned)g.n;
+        rC = buf_rsrc_n((TO*)g.out + (long long)b0 * slab, (long long)((unsigned)g.lines / inner - b0) * slab * eo);
+    } else {
+        rC = buf_rsrc_n((TO*)g.out + (long long)cur.d0 * g.n, (g.lines - cur.d0) * g.n * eo);
+    }
+    const int p00 = p0 + (Y ? MM::row(lg, 0) : lr);
+    const unsigned l00 = cur.d0 + (unsigned)(l0 + (Y ? lr : MM::row(lg, 0)));
+    const unsigned first = (unsigned)p00 * step;
+    const unsigned second = INV ? (unsigned)(g.n - 1 - p00) * step : (unsigned)(p00 + ho) * step;
+#pragma unroll
+    for (int j = 0; j < MD; ++j) {
+        unsigned lo = 0;  // offset of the line (y: the lane's; x: of its register 0)
+        if constexpr (Y) {
+            const unsigned c = l00 + (unsigned)(j * 16), b = c / inner;
+            lo = ((b - b0) * inner * (unsigned)g.n + (c - b * inner)) * eo;
+        } else {
+            lo = (l00 - cur.d0 + (unsigned)(j * 16)) * lstep;
+        }
+#pragma unroll
+        for (int i = 0; i < MP; ++i) {
+            unsigned at[4][2];
+            TM val[4][2];
+            [[maybe_unused]] double old[4][2];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int dp = i * 16 + (Y ? MM::row(0, r) : 0);
+                const unsigned dl = Y ? 0u : (unsigned)MM::row(0, r);
+                const int p = p00 + dp;
+                const bool ok = p < g.h && l00 + (unsigned)(j * 16) + dl < (unsigned)g.lines;
+                const bool ok2 = ok && (INV ? p < ho : !(odd && p == 0));
+                const unsigned base = lo + dl * lstep, ds = (unsigned)dp * step;
+                at[r][0] = ok ? base + first + ds : NOWHERE;
+                at[r][1] = ok2 ? base + (INV ? second - ds : second + ds) : NOWHERE;
+                const TM e = acc[0][i][j][r], o = acc[1][i][j][r];
+                val[r][0] = INV ? e + o : e;
+                val[r][1] = INV ? e - o : o;
+                if (EPI == EPI_ACCUM_F64 && !ok2) val[r][1] = (TM)0;  // not summed
+            }
+            if constexpr (EPI == EPI_ACCUM_F64) {
+                // the eight reads of a register group together
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) old[r][q] = BufIO<double>::ld(rC, at[r][q], 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const double x = old[r][q] + (double)val[r][q];
+                        BufIO<double>::st(x, rC, at[r][q], 0);
+                        se += (double)val[r][q] * (double)val[r][q];
+                        sx += x * x;
+                    }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) BufIO<TO>::st((TO)val[r][q], rC, at[r][q], 0);
+            }
+        }
+    }
+}
+
 template <typename TM, typename TI, typename TO, int EPI, bool Y, bool INV, bool CORR, bool MULTI, int PH, int DN,
           int WP, int WD>
 __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, int nwork,
@@ -149,7 +233,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
     static_assert(sizeof(vec) == 16 && LD >= 1 && NT % BK == 0 && NT % DN == 0 && NT % (4 * PH) == 0, "tile too small for its threads");
     // (a single problem's descriptor stays in the kernel arguments)
     auto desc = [&](const FoldTile& t) -> const FoldDesc& { return MULTI ? work[t.prob] : *work; };
-    constexpr int ei = (int)sizeof(TI), eo = (int)sizeof(TO), em = (int)sizeof(TM);
+    constexpr int ei = (int)sizeof(TI), em = (int)sizeof(TM);
     const int tid = threadIdx.x;
     const int w = tid / 64, l = tid % 64, lr = l % 16, lg = l / 16;
     const int wd = w % C::WAVES_D, wp = w / C::WAVES_D;
@@ -394,11 +478,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                 buf ^= 1;
             }
         }
-        // results.  y lines: rows of the result are modes (or rows k), its
-        // columns lines; x lines the other way round.
         double se = 0.0, sx = 0.0;
-        const int ho = g.n - g.h;       // position of odd slot 0
-        const int odd = g.n & 1;        // slot 0 has no odd mode, row H-1 is its own mirror
         if constexpr (CORR) {
             constexpr double xs = 1.0 / FOLD_XSCALE;
             const double2* rot = g.rot + cur.p0 + wp * WP;
@@ -425,77 +505,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                 }
             }
         }
-        // two results of an element: positions p and ho + p (modes), or rows p
-        // and n - 1 - p.  An offset past any buffer drops the store.
-        constexpr unsigned NOWHERE = 0xffffffffu;
-        const unsigned step = (unsigned)(Y ? g.inner : 1) * eo;   // between positions of a line
-        const unsigned lstep = (unsigned)(Y ? 1 : g.n) * eo;      // between lines of the tile (y: of a slab)
-        __amdgpu_buffer_rsrc_t rC;
-        unsigned inner = 1, b0 = 0;
-        if constexpr (Y) {
-            inner = (unsigned)g.inner;
-            b0 = cur.d0 / inner;
-            const unsigned slab = inner * (unsigned)g.n;
-            rC = buf_rsrc_n((TO*)g.out + (long long)b0 * slab, (long long)((unsigned)g.lines / inner - b0) * slab * eo);
-        } else {
-            rC = buf_rsrc_n((TO*)g.out + (long long)cur.d0 * g.n, (g.lines - cur.d0) * g.n * eo);
-        }
-        const int p00 = cur.p0 + wp * WP + (Y ? MM::row(lg, 0) : lr);
-        const unsigned l00 = cur.d0 + (unsigned)(wd * WD + (Y ? lr : MM::row(lg, 0)));
-        const unsigned first = (unsigned)p00 * step;
-        const unsigned second = INV ? (unsigned)(g.n - 1 - p00) * step : (unsigned)(p00 + ho) * step;
-#pragma unroll
-        for (int j = 0; j < MD; ++j) {
-            unsigned lo = 0;  // offset of the line (y: the lane's; x: of its register 0)
-            if constexpr (Y) {
-                const unsigned c = l00 + (unsigned)(j * 16), b = c / inner;
-                lo = ((b - b0) * inner * (unsigned)g.n + (c - b * inner)) * eo;
-            } else {
-                lo = (l00 - cur.d0 + (unsigned)(j * 16)) * lstep;
-            }
-#pragma unroll
-            for (int i = 0; i < MP; ++i) {
-                unsigned at[4][2];
-                TM val[4][2];
-                [[maybe_unused]] double old[4][2];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int dp = i * 16 + (Y ? MM::row(0, r) : 0);
-                    const unsigned dl = Y ? 0u : (unsigned)MM::row(0, r);
-                    const int p = p00 + dp;
-                    const bool ok = p < g.h && l00 + (unsigned)(j * 16) + dl < (unsigned)g.lines;
-                    const bool ok2 = ok && (INV ? p < ho : !(odd && p == 0));
-                    const unsigned base = lo + dl * lstep, ds = (unsigned)dp * step;
-                    at[r][0] = ok ? base + first + ds : NOWHERE;
-                    at[r][1] = ok2 ? base + (INV ? second - ds : second + ds) : NOWHERE;
-                    const TM e = acc[0][i][j][r], o = acc[1][i][j][r];
-                    val[r][0] = INV ? e + o : e;
-                    val[r][1] = INV ? e - o : o;
-                    if (EPI == EPI_ACCUM_F64 && !ok2) val[r][1] = (TM)0;  // not summed
-                }
-                if constexpr (EPI == EPI_ACCUM_F64) {
-                    // the eight reads of a register group together
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) old[r][q] = BufIO<double>::ld(rC, at[r][q], 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const double x = old[r][q] + (double)val[r][q];
-                            BufIO<double>::st(x, rC, at[r][q], 0);
-                            se += (double)val[r][q] * (double)val[r][q];
-                            sx += x * x;
-                        }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) BufIO<TO>::st((TO)val[r][q], rC, at[r][q], 0);
-                }
-            }
-        }
+        fold_store<TM, TO, EPI, Y, INV, MP, MD>(g, cur, acc, cur.p0 + wp * WP, wd * WD, lr, lg, se, sx);
         if constexpr (EPI == EPI_ACCUM_F64) {
             block_sum2<NT>(se, sx, red);
             if (threadIdx.x == 0) {
@@ -535,7 +545,7 @@ template <typename TM, typename TI, typename TO, int EPI, bool Y, bool INV, bool
 hipError_t launch_fold_typed(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s) {
     if (total <= 0) return hipSuccess;
     if (total > 0x3fffffff || g.lines > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)fold_grid(shape, g.X != nullptr, total));
+    const dim3 grid((unsigned)fold_grid(g, shape, total));
 #define TPT_FOLD(PH_, DN_, WP_, WD_)                                                                              \
     do {                                                                                                          \
         const dim3 nt(FoldCfg<PH_, DN_, WP_, WD_>::NT);                                                           \

@@ -46,6 +46,8 @@ struct DirBasis {
     double* fd_q = nullptr;
     float* fs_qinv = nullptr;
     float* fs_q = nullptr;
+    uint16_t* fb_qinv = nullptr;     // bf16 hi and lo planes
+    uint16_t* fb_q = nullptr;
     // remainders of bases symmetric only up to the rounding of the faces (bf16,
     // scaled, FP64 plans) and the rotation of each slot; null otherwise
     uint16_t* fx_qinv = nullptr;
@@ -72,10 +74,10 @@ struct DirBasis {
 
 // The form of a direction of a plan (host-only plans: dense).  XformKind of
 // its fast transform in fast, -1 = none.
-BasisForm basis_form(const Op1D& op, int precision, bool ylines, int nx, bool no_fast, bool need_dense, int* fast);
+BasisForm basis_form(const Op1D& op, int prec, bool ylines, int nx, bool no_fast, bool need_dense, int* fast);
 // Device-resident cache of eigenbases keyed by (device, faces, BC, location,
-// form); the host eigen data is shared by the forms.
-std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, bool host_only,
+// form, precision of the products); the host eigen data is shared by all.
+std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, int prec, bool host_only,
                                           std::string& err);
 size_t basis_cache_bytes();   // device bytes held by live cached bases
 

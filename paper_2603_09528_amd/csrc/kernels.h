@@ -108,7 +108,8 @@ hipError_t launch_gemm_bf16(const GemmDesc& g, const GemmDesc* d_work, int nwork
 // Transform of one mirror-symmetric direction by two half-size products (see
 // fold_impl.h): every line of the direction, x lines contiguous, y lines the
 // columns of each z slab (column c = slab * inner + i).  P holds the padded
-// even and odd bases, [2][hp][kp] of the compute type; the modes of a line
+// even and odd bases by K step, in the compute type or as BF16 hi and lo
+// planes; the modes of a line
 // are kept even ones first.  X and rot: the remainders and rotations of a
 // basis that is symmetric only up to rounding (FP64), or null.
 struct FoldDesc {
@@ -118,7 +119,8 @@ struct FoldDesc {
     const void* in;
     void* out;
     int n, h;               // line length and (n + 1) / 2
-    int hp, kp;             // h rounded up to FOLD_ROWS and FOLD_COLS
+    int hp, kp;             // h rounded up to FOLD_ROWS and fold_cols(prec)
+    int prec;               // GemmPrec
     int ylines, inverse;
     int inner;              // y lines: Nx
     long long lines;        // x: Ny Nz nrhs; y: Nx Nz nrhs
@@ -130,28 +132,31 @@ struct FoldDesc {
 };
 enum { FOLD_ROWS = 64, FOLD_COLS = 16, FOLD_MIN_N = 16, FOLD_COARSE = 32 };
 constexpr double FOLD_XSCALE = 16777216.0;  // of the remainders (2^24)
-// Tile shapes: slots x lines (64 x 64 instead of 64 x 128 with remainders).
+// Tile shapes: slots x lines (with remainders 64 x 64 instead of 64 x 128; split
+// BF16 has 64 x 128 and, in place of 32 x 128, 32 x 64).
 enum FoldShape { FOLD_64x128 = 0, FOLD_32x128 = 1, FOLD_16x64 = 2, FOLD_NSHAPE = 3 };
 // Whether a direction of n unknowns of an nx x ny plane (ylines: n = ny) fits
 // the kernel's 32-bit offsets.
-bool fold_fits(int n, int nx, bool ylines);
+bool fold_fits(int n, int nx, bool ylines, int prec);
+// Columns of a K step, to which the bases are padded.
+inline int fold_cols(int prec) { return prec == GP_BF16X3 ? 32 : FOLD_COLS; }
 // Tile shape of one launch over `count` problems (all with remainders, or none;
 // every shape gives the same bits).
 int fold_shape(const FoldDesc* g, int count);
 long long fold_tiles(FoldDesc& g, int shape);       // sets tiles_p; the tile count
 // Blocks of a launch of `total` tiles: at most what the GPU holds at once (two
 // blocks of eight waves, three of four, five of the small tile per CU).
-long long fold_grid(int shape, bool corr, long long total);
+long long fold_grid(const FoldDesc& g, int shape, long long total);
 struct FoldList {           // device arrays of a launch over several problems
     const FoldDesc* work;   // block_begin and tiles_p set
     int nwork;
     const unsigned* coarse; // the problem of tiles 0, FOLD_COARSE, 2 FOLD_COARSE, ..
 };
 std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long total);
-hipError_t launch_fold(FoldDesc g, int prec, hipStream_t s);
-hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int prec, int shape,
-                             hipStream_t s);
+hipError_t launch_fold(FoldDesc g, hipStream_t s);
+hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
+hipError_t launch_fold_bf16(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f32(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 
 // Fast transforms of the lines of a uniform direction (analytic bases:

@@ -443,7 +443,7 @@ int MultiExec::enqueue(hipStream_t s) const {
                 TimedScope ts("multi_gemm", s);
                 const FoldDesc& rep = *(const FoldDesc*)(blob_.data() + L.off);
                 const FoldList list{(const FoldDesc*)(d_desc_ + L.off), L.nwork, (const unsigned*)(d_desc_ + L.off2)};
-                e = launch_fold_multi(rep, list, L.total, L.prec, L.variant, s);
+                e = launch_fold_multi(rep, list, L.total, L.variant, s);
                 break;
             }
             case 8: {

@@ -48,7 +48,7 @@ static std::mutex g_cache_mu;
 static std::map<std::string, std::weak_ptr<DirBasis>> g_cache;
 static std::map<std::string, std::weak_ptr<const Eig1D>> g_eig_cache;
 
-BasisForm basis_form(const Op1D& op, int precision, bool ylines, int nx, bool no_fast, bool need_dense, int* fast) {
+BasisForm basis_form(const Op1D& op, int prec, bool ylines, int nx, bool no_fast, bool need_dense, int* fast) {
     *fast = -1;
     if (!no_fast && op.uniform && fft_supported(op.n)) {
         if (op.periodic) *fast = UT_FOURIER;
@@ -56,8 +56,7 @@ BasisForm basis_form(const Op1D& op, int precision, bool ylines, int nx, bool no
         else if (op.loc == LOC_C && op.bc_lo == BC_D && op.bc_hi == BC_D) *fast = UT_DST;
         if (*fast >= 0) return BF_FAST;
     }
-    // the split-BF16 products read whole bases
-    if (op.mirror && !need_dense && precision != TPT_MIXED_BF16X3 && fold_fits(op.n, nx, ylines)) return BF_FOLD;
+    if (op.mirror && !need_dense && fold_fits(op.n, nx, ylines, prec)) return BF_FOLD;
     return BF_DENSE;
 }
 
@@ -70,7 +69,7 @@ static std::string eig_key(const Op1D& op, int ncells, const double* faces) {
     return k;
 }
 
-std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, bool host_only,
+std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const double* faces, int form, int prec, bool host_only,
                                           std::string& err) {
     int device = 0;
     if (!host_only) {
@@ -80,7 +79,8 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
         }
     }
     const std::string ekey = eig_key(op, ncells, faces);
-    int hdr[3] = {device, host_only ? 1 : 0, form};
+    if (form != BF_FOLD) prec = GP_F64;  // one set for all precisions
+    int hdr[4] = {device, host_only ? 1 : 0, form, prec};
     const std::string key = std::string((const char*)hdr, sizeof(hdr)) + ekey;
     std::lock_guard<std::mutex> lock(g_cache_mu);
     auto it = g_cache.find(key);
@@ -103,7 +103,7 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
     const Eig1D& eig = *b->eig;
     // an eigenbasis that does not split after all takes the dense product
     const int h = (op.n + 1) / 2;
-    const int hp = (h + FOLD_ROWS - 1) / FOLD_ROWS * FOLD_ROWS, kp = (h + FOLD_COLS - 1) / FOLD_COLS * FOLD_COLS;
+    const int hp = (h + FOLD_ROWS - 1) / FOLD_ROWS * FOLD_ROWS, kp = (h + fold_cols(prec) - 1) / fold_cols(prec) * fold_cols(prec);
     FoldBasis fb;
     if (form == BF_FOLD && !fold_basis(op, eig, hp, kp, fb)) b->form = form = BF_DENSE;
     b->null_pos = form == BF_FOLD && eig.null_index >= 0 ? eig.null_index / 2 : eig.null_index;
@@ -128,10 +128,10 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             o_tw = take(16 * (size_t)(n / 2));
             o_qtw = take(16 * (size_t)(n / 2 + 1));
         } else if (form == BF_FOLD) {
-            o_qinv = take(8 * nf);
-            o_q = take(8 * nf);
-            o_sqinv = take(4 * nf);
-            o_sq = take(4 * nf);
+            if (prec != GP_F64) fb.rotated = false;
+            const size_t es = prec == GP_F64 ? 8 : 4;  // (two bf16 planes: 4 bytes)
+            o_qinv = take(es * nf);
+            o_q = take(es * nf);
             if (fb.rotated) {
                 o_xqinv = take(2 * nf);
                 o_xq = take(2 * nf);
@@ -178,13 +178,27 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             };
             double* dqinv = (double*)(host.data() + o_qinv);
             double* dq = (double*)(host.data() + o_q);
-            float* sqinv = (float*)(host.data() + o_sqinv);
-            float* sq = (float*)(host.data() + o_sq);
+            float* sqinv = (float*)(host.data() + o_qinv);
+            float* sq = (float*)(host.data() + o_q);
+            uint16_t* bqinv = (uint16_t*)(host.data() + o_qinv);
+            uint16_t* bq = (uint16_t*)(host.data() + o_q);
             for (size_t e = 0; e < nf; ++e) {
-                dqinv[at(e, 8)] = fb.fwd[e];
-                dq[at(e, 8)] = fb.inv[e];
-                sqinv[at(e, 16)] = (float)fb.fwd[e];
-                sq[at(e, 16)] = (float)fb.inv[e];
+                if (prec == GP_F64) {
+                    dqinv[at(e, 8)] = fb.fwd[e];
+                    dq[at(e, 8)] = fb.inv[e];
+                } else if (prec == GP_F32) {
+                    sqinv[at(e, 16)] = (float)fb.fwd[e];
+                    sq[at(e, 16)] = (float)fb.inv[e];
+                } else {
+                    // [step of 32][parity][hi, lo][row][32]
+                    const size_t par = e / ((size_t)hp * kp), row = e / kp % hp, c = e % kp;
+                    const size_t o = ((c / 32 * 2 + par) * 2 * hp + row) * 32 + c % 32;
+                    const uint16_t hi = host_bf16((float)fb.fwd[e]), hj = host_bf16((float)fb.inv[e]);
+                    bqinv[o] = hi;
+                    bqinv[o + (size_t)hp * 32] = host_bf16((float)(fb.fwd[e] - (double)host_bf16_to_f(hi)));
+                    bq[o] = hj;
+                    bq[o + (size_t)hp * 32] = host_bf16((float)(fb.inv[e] - (double)host_bf16_to_f(hj)));
+                }
             }
             if (fb.rotated) {
                 uint16_t* xi = (uint16_t*)(host.data() + o_xqinv);
@@ -246,10 +260,16 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
         } else if (form == BF_FOLD) {
             b->hp = hp;
             b->kp = kp;
-            b->fd_qinv = (double*)(d + o_qinv);
-            b->fd_q = (double*)(d + o_q);
-            b->fs_qinv = (float*)(d + o_sqinv);
-            b->fs_q = (float*)(d + o_sq);
+            if (prec == GP_F64) {
+                b->fd_qinv = (double*)(d + o_qinv);
+                b->fd_q = (double*)(d + o_q);
+            } else if (prec == GP_F32) {
+                b->fs_qinv = (float*)(d + o_qinv);
+                b->fs_q = (float*)(d + o_q);
+            } else {
+                b->fb_qinv = (uint16_t*)(d + o_qinv);
+                b->fb_q = (uint16_t*)(d + o_q);
+            }
             if (fb.rotated) {
                 b->fx_qinv = (uint16_t*)(d + o_xqinv);
                 b->fx_q = (uint16_t*)(d + o_xq);
@@ -397,13 +417,13 @@ int tpt_plan_create(const tpt_plan_desc* desc, tpt_plan* out) {
                      (p->N[0] == 128 || p->N[0] == 256) && p->N[1] % 128 == 0;
     int fast[2] = {-1, -1}, form[2] = {BF_DENSE, BF_DENSE};
     for (int d = 0; d < 2 && !p->host_only; ++d)
-        form[d] = basis_form(p->op[d], desc->precision, d == 1, p->N[0],
+        form[d] = basis_form(p->op[d], plan_gemm_prec(p.get()), d == 1, p->N[0],
                              (desc->flags & (d == 0 ? TPT_FLAG_DENSE_X : TPT_FLAG_DENSE_Y)) != 0,
                              d == 1 && want_fuse && fast[0] >= 0, &fast[d]);
     std::string err;
-    p->bx = basis_cache_get(p->op[0], desc->n[0], p->faces[0].data(), form[0], p->host_only, err);
+    p->bx = basis_cache_get(p->op[0], desc->n[0], p->faces[0].data(), form[0], plan_gemm_prec(p.get()), p->host_only, err);
     if (!p->bx) return fail(err.find("memory") != std::string::npos ? TPT_ERR_OOM : TPT_ERR_INVALID, "x basis: " + err);
-    p->by = basis_cache_get(p->op[1], desc->n[1], p->faces[1].data(), form[1], p->host_only, err);
+    p->by = basis_cache_get(p->op[1], desc->n[1], p->faces[1].data(), form[1], plan_gemm_prec(p.get()), p->host_only, err);
     if (!p->by) return fail(err.find("memory") != std::string::npos ? TPT_ERR_OOM : TPT_ERR_INVALID, "y basis: " + err);
     if (desc->kind == TPT_POISSON) {
         p->sigma = 0.0;

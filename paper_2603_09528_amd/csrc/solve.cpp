@@ -208,7 +208,10 @@ FoldDesc stage_fold(const tpt_plan_s* p, int stage, const void* in, int tin, voi
     const bool xdir = stage == ST_XF || stage == ST_XI, fwd = stage == ST_XF || stage == ST_YF;
     const DirBasis* b = xdir ? p->bx.get() : p->by.get();
     FoldDesc g{};
-    if (plan_gemm_prec(p) == GP_F64) {
+    g.prec = plan_gemm_prec(p);
+    if (g.prec == GP_BF16X3) {
+        g.P = fwd ? b->fb_qinv : b->fb_q;
+    } else if (g.prec == GP_F64) {
         g.P = fwd ? b->fd_qinv : b->fd_q;
         g.X = fwd ? b->fx_qinv : b->fx_q;
         g.rot = b->f_rot;
@@ -374,7 +377,7 @@ static int run_stage(const tpt_plan_s* p, int stage, int prec, const void* in, i
         FoldDesc g = stage_fold(p, stage, in, tin, out, tout, epi, partials, nrhs);
         if (nblocks) *nblocks = fold_tiles(g, fold_shape(&g, 1));
         TimedScope ts(stage_name(stage, prec), s);
-        hipError_t e = launch_fold(g, prec, s);
+        hipError_t e = launch_fold(g, s);
         if (e != hipSuccess) return fail(TPT_ERR_HIP, std::string("transform launch: ") + hipGetErrorString(e));
         return TPT_OK;
     }

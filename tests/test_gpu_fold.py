@@ -18,7 +18,7 @@ def _T():
     return T
 
 
-TOL = {"fp64": 1e-12, "fp32": 1e-10}
+TOL = {"fp64": 1e-12, "fp32": 1e-10, "bf16x3": 1e-10}
 
 EDGE = [
     ((16, 17, 6), (1.5, 1.0, 1.0), (W.NN, W.DD, W.DD), "CCC"),
@@ -32,7 +32,7 @@ EDGE = [
 ]
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
 @pytest.mark.parametrize("case", EDGE, ids=lambda c: "x".join(map(str, c[0])))
 def test_edges_match_oracle(case, prec):
     n, beta, bc, loc = case
@@ -46,7 +46,7 @@ def test_edges_match_oracle(case, prec):
     assert err <= TOL[prec], err
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
 @pytest.mark.parametrize("n,bc", [((128, 256, 256), (W.NN, W.DD, W.NN)), ((256, 64, 520), (W.DD, W.NN, W.DD)),
                                   ((64, 128, 130), (W.PP, W.PP, W.DD))], ids=str)
 def test_large_tiles_match_fast_transforms(n, bc, prec):
@@ -55,7 +55,7 @@ def test_large_tiles_match_fast_transforms(n, bc, prec):
     (1e-12 relative; a mixed solve to its refinement target)."""
     p = W.make_problem(n, (0.0, 0.0, 1.5), bc)
     f = np.stack([W.rhs(p, 3 + i) for i in range(2)])
-    kw = dict(nrhs=2) if prec == "fp64" else dict(nrhs=2, precision=prec, fixed_refine=3)
+    kw = dict(nrhs=2) if prec == "fp64" else dict(nrhs=2, precision=prec, fixed_refine=4)
     T = _T()
     say(n, bc, prec)
     fast = T.Plan.from_problem(p, **kw)
