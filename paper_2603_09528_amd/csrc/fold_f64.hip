@@ -37,6 +37,8 @@ long long fold_tiles(FoldDesc& g, int shape) {
 // 46, 45 and 36); small cases it decides: 192 x 160 x 128, x lines, 31 us in
 // 32 x 128 against 36 in 64 x 64 (remainders) and 26 against 38 in 64 x 128;
 // 64 x 48 x 64, 6-8 us in 16 x 64 against 8 us.
+// Split BF16, 64 x 128 and 32 x 64: 128^3, 6.3-9.4 and 5.7-7.7 us; 256 x 200 x 100,
+// x 17-19 and 16-17, y 14 and 17.
 static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
     static const double rate[3][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.92, 0.55}, {1.0, 0.7, 0.0}};
     int ph, dn;
