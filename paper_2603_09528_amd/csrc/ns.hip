@@ -28,13 +28,17 @@
 // the Dirichlet rows of the 1-D operators, face-located along the
 // component's own direction).
 //
-// Memory-bound kernels.  The explicit kernel of a component reads the
-// component, the two transverse components, P and E^{k-1} and writes E^k
-// and rhs: 56 B per unknown (48 B for k = 1).  A thread marches one (i, j)
-// column through a chunk of z planes with the z neighbours in registers;
-// in-plane neighbours are cache hits of the adjacent lanes and rows.  The
-// pressure update rides in the gradient update's pass (which reads Phi
-// anyway): 16 B per cell more there, P read and written.
+// Memory-bound.  One kernel forms the explicit terms and right-hand sides of
+// all three components: u, v, w, P and the three E^{k-1} are read and the E^k
+// and the right-hand sides written once, 104 B per cell (80 B for k = 1; a
+// kernel for each component moves 168).  512 x 256 x 256, no implicit
+// diffusion: 1726 us a substep in three kernels, 877 in one (3.8 TB/s).  A
+// thread marches one (i, j) column of cells through a chunk of z planes with
+// the z neighbours in registers; x neighbours come from the lanes beside
+// (as loads they took the first-level cache's time: 1146 us), y neighbours
+// are cache hits of the adjacent rows.  The pressure update rides in the gradient
+// update's pass (which reads Phi anyway): 16 B per cell more there, P read
+// and written.
 #include <algorithm>
 #include <cmath>
 #include <memory>
@@ -54,198 +58,222 @@ struct NsDesc {
     int N[3];                   // cells per direction
     int nf[3];                  // face unknowns per direction (N periodic, N - 1 walls)
     int per[3];
-    int impl[3];                // direction in L_I
     const double* w[3];         // cell widths
     const double* h[3];         // face spacings: distance of the centres of cells m, m+1
-    const double* ca[3];        // 1-D operator of this component, per direction
-    const double* cb[3];
-    const double* cc[3];
+    const double* ca[2][3];     // 1-D operators [at cells, at faces][direction]
+    const double* cb[2][3];
+    const double* cc[2][3];
     const double* q[3];         // u, v, w (u^k)
     const double* P;            // P^{k-1/2}
-    double* e;                  // E^{k-1} in (if use_prev), E^k out
-    double* rhs;                // Helmholtz right-hand side (u* for L_I = 0)
+    double* e[3];               // E^{k-1} in (if use_prev), E^k out
+    double* rhs[3];             // Helmholtz right-hand sides (u* for L_I = 0)
     double dt, nu, alpha, beta, gamma, cn;
     int use_prev;
+    int rz;                     // z planes one thread marches through
 };
 
 namespace {
 
 constexpr int NS_NT = 256;
-constexpr int NS_RZ = 32;   // z planes one thread marches through
 
-// Column blocks of a plane of ncol columns times chunks of NS_RZ planes.
-inline long long ns_blocks(long long ncol, int nplanes) {
-    return ((ncol + NS_NT - 1) / NS_NT) * ((nplanes + NS_RZ - 1) / NS_RZ);
+// Planes of a thread's chunk: 32 (each chunk reads a plane of the one below it
+// again: 928 us in chunks of 8, 877 in 32 at 512 x 256 x 256), fewer where
+// that leaves less than two rounds of the three blocks a compute unit holds
+// (192 x 160 x 128: 120 us in chunks of 32, 110 in 11), down to 4.
+inline int ns_chunk(long long ncb, int nz) {
+    const long long n = std::min<long long>(std::max<long long>((2 * 3 * 256 + ncb - 1) / ncb, (nz + 31) / 32), (nz + 3) / 4);
+    return (int)((nz + n - 1) / n);
 }
 
-// Offsets of the two neighbours along an in-plane direction (wrapped if
-// periodic); hm / hp are false where the neighbour is a wall.
-struct Nb {
-    long long m, p;
-    bool hm, hp;
+// Read-only memory through the scalar cache (uniform indices): the stores of
+// the kernel may not alias it.
+typedef const double __attribute__((address_space(4)))* cptr;
+__device__ __forceinline__ cptr as_const(const double* p) { return (cptr)p; }
+
+// Value of the lane below / above.
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double x) {
+    const int2 v = __builtin_bit_cast(int2, x);
+    const int2 r = {__builtin_amdgcn_update_dpp(0, v.x, CTRL, 0xf, 0xf, false),
+                    __builtin_amdgcn_update_dpp(0, v.y, CTRL, 0xf, 0xf, false)};
+    return __builtin_bit_cast(double, r);
+}
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;  // from lane + 1, from lane - 1
+
+// 1-D operator row applied along a direction.
+struct Row {
+    double a, b, c;
+    __device__ __forceinline__ double operator()(double m, double q, double p) const { return b * q + a * m + c * p; }
 };
-__device__ __forceinline__ Nb ns_nb(int pos, int n, long long stride, int periodic) {
-    Nb b;
-    b.hm = pos > 0 || periodic;
-    b.hp = pos < n - 1 || periodic;
-    b.m = pos > 0 ? -stride : (long long)(n - 1) * stride;
-    b.p = pos < n - 1 ? stride : -(long long)(n - 1) * stride;
-    return b;
+
+// The diffusion of a component split into its implicit and explicit parts,
+// the last NI of the directions x, y, z being implicit.
+template <int NI>
+__device__ __forceinline__ void ns_diffusion(double lx, double ly, double lz, double& li, double& le) {
+    li = (NI > 2 ? lx : 0.0) + (NI > 1 ? ly : 0.0) + (NI > 0 ? lz : 0.0);
+    le = (NI > 2 ? 0.0 : lx) + (NI > 1 ? 0.0 : ly) + (NI > 0 ? 0.0 : lz);
 }
 
-// Explicit terms and right-hand side of u (C = 0) or v (C = 1).  A thread
-// owns one (i, j) column of the component and marches it up NS_RZ planes,
-// carrying the z neighbours of the component and the z-face mass flux below
-// the current plane in registers; in-plane neighbours are cache hits of the
-// adjacent lanes and rows (neighbouring rows run on one XCD).
-template <int C>
-__global__ __launch_bounds__(NS_NT) void ns_explicit_xy_kernel(NsDesc d) {
-    constexpr int T = 1 - C;                        // the other in-plane direction
-    const int ext[2] = {C == 0 ? d.nf[0] : d.N[0], C == 1 ? d.nf[1] : d.N[1]};
-    const int nz = d.N[2];
-    const long long sxy = (long long)ext[0] * ext[1];
-    const long long ncb = (sxy + NS_NT - 1) / NS_NT;
+// Explicit terms and right-hand sides of u on face i, v on face j and w on
+// face k of the cells (i, j, k) of a thread's column.  Every value is loaded
+// where it exists and from a valid neighbouring address where it does not (a
+// wall), then replaced by zero.  A plane takes 11 loads of velocity and
+// pressure, seven of them cache hits of the rows next to this one
+// (neighbouring rows run on one XCD); what plane k + 1 needs of plane k and
+// of itself at k is carried: u at faces i and i - 1, v at j and j - 1, w at
+// (i, j), (i + 1, j) and (i, j + 1), and P.
+template <int NI>
+__global__ __launch_bounds__(NS_NT, 3) void ns_explicit_kernel(NsDesc d) {
+    const int nx = d.N[0], ny = d.N[1], nz = d.N[2], nux = d.nf[0], nvy = d.nf[1], nwz = d.nf[2];
+    const long long pxy = (long long)nx * ny, uxy = (long long)nux * ny, vxy = (long long)nx * nvy;
+    const long long ncb = (pxy + NS_NT - 1) / NS_NT;
     const long long lb = xcd_block(blockIdx.x, gridDim.x);
     const long long zc = lb / ncb;
-    const long long col = (lb - zc * ncb) * NS_NT + threadIdx.x;
-    if (col >= sxy) return;
-    const int j = (int)(col / ext[0]), i = (int)(col - (long long)j * ext[0]);
-    const int idx[2] = {i, j};
-    const int k0 = (int)zc * NS_RZ, k1 = min(nz, k0 + NS_RZ);
-    const Nb nb[2] = {ns_nb(i, ext[0], 1, d.per[0]), ns_nb(j, ext[1], ext[0], d.per[1])};
-    const double ax = d.ca[0][i], bx = d.cb[0][i], cx = d.cc[0][i];
-    const double ay = d.ca[1][j], by = d.cb[1][j], cy = d.cc[1][j];
-    const int m = idx[C];
-    const int m1 = m + 1 < d.N[C] ? m + 1 : 0;
-    const double hC = d.h[C][m], w0 = d.w[C][m], w1 = d.w[C][m1];
-    const double wT = d.w[T][idx[T]];
-    // component T: cells along C, faces along T (plane tx0 x tx1)
-    const int tx0 = T == 0 ? d.nf[0] : d.N[0];
-    const long long tsxy = (long long)tx0 * (T == 1 ? d.nf[1] : d.N[1]);
-    const long long tst[2] = {1, tx0};
-    const int jT = idx[T];
-    const bool tt = jT < d.nf[T];
-    const int jb = jT > 0 ? jT - 1 : (d.per[T] ? d.nf[T] - 1 : -1);
-    const long long to0 = (long long)m * tst[C], to1 = (long long)m1 * tst[C];
-    const long long tjt = (long long)jT * tst[T], tjb = (long long)(jb > 0 ? jb : 0) * tst[T];
-    // w and P: planes of N0 x N1 cells
-    const long long psxy = (long long)d.N[0] * d.N[1];
-    const long long pst[2] = {1, d.N[0]};
-    const long long po0 = (long long)m * pst[C] + (long long)idx[T] * pst[T];
-    const long long po1 = (long long)m1 * pst[C] + (long long)idx[T] * pst[T];
-    const double* Q = d.q[C];
-    const double* Qt = d.q[T];
-    const double* Qw = d.q[2];
-    double q0 = Q[(long long)k0 * sxy + col];
-    double qzm = k0 > 0 ? Q[(long long)(k0 - 1) * sxy + col] : (d.per[2] ? Q[(long long)(nz - 1) * sxy + col] : 0.0);
-    const int kb = k0 > 0 ? k0 - 1 : (d.per[2] ? d.nf[2] - 1 : -1);
-    double fzb = kb >= 0 ? 0.5 * (w0 * Qw[(long long)kb * psxy + po0] + w1 * Qw[(long long)kb * psxy + po1]) : 0.0;
+    const unsigned col = (unsigned)(lb - zc * ncb) * NS_NT + threadIdx.x;  // (a plane has fewer than 2^31 cells)
+    if (col >= pxy) return;
+    const int j = (int)(col / (unsigned)nx), i = (int)(col - (unsigned)j * nx);
+    const int k0 = (int)zc * d.rz, k1 = min(nz, k0 + d.rz);
+    // neighbours: cells i +- 1, j +- 1 and faces; wrapped, or clamped at a wall
+    const bool hu = i < nux, hv = j < nvy;             // the faces above the cell
+    const bool cxm = i > 0 || d.per[0], cxp = i + 1 < nx || d.per[0];   // cells beside
+    const bool cym = j > 0 || d.per[1], cyp = j + 1 < ny || d.per[1];
+    const bool fxp = i + 1 < nux || d.per[0], fyp = j + 1 < nvy || d.per[1];   // faces beside (below: cxm, cym)
+    const int im = i > 0 ? i - 1 : (d.per[0] ? nx - 1 : 0), ip = i + 1 < nx ? i + 1 : (d.per[0] ? 0 : i);
+    const int jm = j > 0 ? j - 1 : (d.per[1] ? ny - 1 : 0), jp = j + 1 < ny ? j + 1 : (d.per[1] ? 0 : j);
+    const int fi = min(i, nux - 1), fim = min(im, nux - 1), fip = min(ip, nux - 1);
+    const int fj = min(j, nvy - 1), fjm = min(jm, nvy - 1), fjp = min(jp, nvy - 1);
+    unsigned u00 = (unsigned)j * nux + fi, um0 = (unsigned)j * nux + fim, up0 = (unsigned)j * nux + fip;
+    unsigned u0m = (unsigned)jm * nux + fi, u0p = (unsigned)jp * nux + fi, ump = (unsigned)jp * nux + fim;
+    unsigned v00 = (unsigned)fj * nx + i, v0m = (unsigned)fjm * nx + i, v0p = (unsigned)fjp * nx + i;
+    unsigned vm0 = (unsigned)fj * nx + im, vp0 = (unsigned)fj * nx + ip, vpm = (unsigned)fjm * nx + ip;
+    unsigned cm0 = (unsigned)j * nx + im, cp0 = (unsigned)j * nx + ip;
+    unsigned c0m = (unsigned)jm * nx + i, c0p = (unsigned)jp * nx + i;
+    // the x neighbours come from the lanes beside, at the end of a wave and of a row from memory
+    const int lane = threadIdx.x % 64;
+    const bool inl = lane > 0 && i > 0, inr = lane < 63 && i + 1 < nx;
+    const bool edl = !inl && cxm, edr = !inr && cxp;
+    auto zrow = [&](int face, int k) { return Row{as_const(d.ca[face][2])[k], as_const(d.cb[face][2])[k], as_const(d.cc[face][2])[k]}; };
+    const cptr wz = as_const(d.w[2]), hz = as_const(d.h[2]);
+    auto row = [&](int face, int dir, int m) { return Row{d.ca[face][dir][m], d.cb[face][dir][m], d.cc[face][dir][m]}; };
+    const Row rfx = row(1, 0, fi), rcx = row(0, 0, i), rfy = row(1, 1, fj), rcy = row(0, 1, j);
+    const double wx0 = d.w[0][i], wx1 = d.w[0][ip], wy0 = d.w[1][j], wy1 = d.w[1][jp];
+    const double rhx = 1.0 / d.h[0][fi], rhy = 1.0 / d.h[1][fj], rwx = 1.0 / wx0, rwy = 1.0 / wy0;
+    const double* U = d.q[0] + (long long)k0 * uxy;
+    const double* V = d.q[1] + (long long)k0 * vxy;
+    const double* W = d.q[2] + (long long)k0 * pxy;
+    const double* P = d.P + (long long)k0 * pxy;
+    // plane k0 and what it needs of the plane below
+    double u = hu ? U[u00] : 0.0, ul = cxm ? U[um0] : 0.0;   // ul: face i - 1
+    double v = hv ? V[v00] : 0.0, vl = cym ? V[v0m] : 0.0;
+    double w = k0 < nwz ? W[col] : 0.0, p = P[col];
+    const bool below = k0 > 0 || d.per[2];
+    const long long kb = k0 > 0 ? -1 : (below ? nz - 1 : 0);
+    double ub = hu && below ? U[kb * uxy + u00] : 0.0;
+    double vb = hv && below ? V[kb * vxy + v00] : 0.0;
+    const double* Wb = W + (k0 > 0 ? -1 : (below ? nwz - 1 : 0)) * pxy;
+    double wb = below ? Wb[col] : 0.0, wbx = below ? Wb[cp0] : 0.0, wby = below ? Wb[c0p] : 0.0;
     for (int k = k0; k < k1; ++k) {
-        const long long o = (long long)k * sxy + col;
-        const double qzp = k + 1 < nz ? Q[o + sxy] : (d.per[2] ? Q[col] : 0.0);
-        const double qxm = nb[0].hm ? Q[o + nb[0].m] : 0.0, qxp = nb[0].hp ? Q[o + nb[0].p] : 0.0;
-        const double qym = nb[1].hm ? Q[o + nb[1].m] : 0.0, qyp = nb[1].hp ? Q[o + nb[1].p] : 0.0;
-        const double lx = bx * q0 + ax * qxm + cx * qxp;
-        const double ly = by * q0 + ay * qym + cy * qyp;
-        const double lz = d.cb[2][k] * q0 + d.ca[2][k] * qzm + d.cc[2][k] * qzp;
-        const double li = (d.impl[0] ? lx : 0.0) + (d.impl[1] ? ly : 0.0) + (d.impl[2] ? lz : 0.0);
-        const double le = (d.impl[0] ? 0.0 : lx) + (d.impl[1] ? 0.0 : ly) + (d.impl[2] ? 0.0 : lz);
-        const double qcm = C == 0 ? qxm : qym, qcp = C == 0 ? qxp : qyp;
-        const double qtm = C == 0 ? qym : qxm, qtp = C == 0 ? qyp : qxp;
-        // along C: fluxes through the cell centres on both sides of face m
-        const double ul = 0.5 * (qcm + q0), uh = 0.5 * (q0 + qcp);
-        double adv = -(uh * uh - ul * ul) / hC;
-        // across T: component T's face velocities, width-weighted over cells m, m1
-        const long long tk = (long long)k * tsxy;
-        const double ft = tt ? 0.5 * (w0 * Qt[tk + to0 + tjt] + w1 * Qt[tk + to1 + tjt]) : 0.0;
-        const double fb = jb >= 0 ? 0.5 * (w0 * Qt[tk + to0 + tjb] + w1 * Qt[tk + to1 + tjb]) : 0.0;
-        adv -= (ft * (0.5 * (q0 + qtp)) - fb * (0.5 * (q0 + qtm))) / (hC * wT);
-        // across z: w on the face above plane k (the one below is carried)
-        const long long pk = (long long)k * psxy;
-        const double fzt = k < d.nf[2] ? 0.5 * (w0 * Qw[pk + po0] + w1 * Qw[pk + po1]) : 0.0;
-        adv -= (fzt * (0.5 * (q0 + qzp)) - fzb * (0.5 * (q0 + qzm))) / (hC * d.w[2][k]);
-        const double gp = (d.P[pk + po1] - d.P[pk + po0]) / hC;
-        const double ek = adv + d.nu * le;
-        double r = q0 + d.dt * (d.alpha * ek - d.gamma * gp) + d.cn * li;
-        if (d.use_prev) r += d.dt * d.beta * d.e[o];
-        d.e[o] = ek;
-        d.rhs[o] = r;
-        fzb = fzt;
-        qzm = q0;
-        q0 = qzp;
-    }
-}
-
-// Explicit terms and right-hand side of w (faces along z): a thread owns an
-// (i, j) column of cells and marches the z faces; the transverse velocities
-// and the pressure of the cell above face k are carried to face k + 1.
-__global__ __launch_bounds__(NS_NT) void ns_explicit_z_kernel(NsDesc d) {
-    const int nx = d.N[0], ny = d.N[1], nz = d.N[2], nzf = d.nf[2];
-    const long long sxy = (long long)nx * ny;
-    const long long ncb = (sxy + NS_NT - 1) / NS_NT;
-    const long long lb = xcd_block(blockIdx.x, gridDim.x);
-    const long long zc = lb / ncb;
-    const long long col = (lb - zc * ncb) * NS_NT + threadIdx.x;
-    if (col >= sxy) return;
-    const int j = (int)(col / nx), i = (int)(col - (long long)j * nx);
-    const int k0 = (int)zc * NS_RZ, k1 = min(nzf, k0 + NS_RZ);
-    const Nb nbx = ns_nb(i, nx, 1, d.per[0]), nby = ns_nb(j, ny, nx, d.per[1]);
-    const double ax = d.ca[0][i], bx = d.cb[0][i], cx = d.cc[0][i];
-    const double ay = d.ca[1][j], by = d.cb[1][j], cy = d.cc[1][j];
-    const double wx = d.w[0][i], wy = d.w[1][j];
-    // u: planes of nf0 x ny, x faces i (above) and i - 1 (below)
-    const long long usxy = (long long)d.nf[0] * ny;
-    const bool ut = i < d.nf[0];
-    const int ib = i > 0 ? i - 1 : (d.per[0] ? d.nf[0] - 1 : -1);
-    const long long uot = (long long)j * d.nf[0] + i, uob = (long long)j * d.nf[0] + (ib > 0 ? ib : 0);
-    // v: planes of nx x nf1, y faces j and j - 1
-    const long long vsxy = (long long)nx * d.nf[1];
-    const bool vt = j < d.nf[1];
-    const int jbv = j > 0 ? j - 1 : (d.per[1] ? d.nf[1] - 1 : -1);
-    const long long vot = (long long)j * nx + i, vob = (long long)(jbv > 0 ? jbv : 0) * nx + i;
-    const double* Q = d.q[2];
-    const double* U = d.q[0];
-    const double* V = d.q[1];
-    auto cell = [&](int m, double& ut_, double& ub_, double& vt_, double& vb_, double& p_) {
-        ut_ = ut ? U[(long long)m * usxy + uot] : 0.0;
-        ub_ = ib >= 0 ? U[(long long)m * usxy + uob] : 0.0;
-        vt_ = vt ? V[(long long)m * vsxy + vot] : 0.0;
-        vb_ = jbv >= 0 ? V[(long long)m * vsxy + vob] : 0.0;
-        p_ = d.P[(long long)m * sxy + col];
-    };
-    double ut0, ub0, vt0, vb0, p0;
-    cell(k0, ut0, ub0, vt0, vb0, p0);
-    double q0 = Q[(long long)k0 * sxy + col];
-    double qzm = k0 > 0 ? Q[(long long)(k0 - 1) * sxy + col] : (d.per[2] ? Q[(long long)(nzf - 1) * sxy + col] : 0.0);
-    for (int k = k0; k < k1; ++k) {
-        const long long o = (long long)k * sxy + col;
-        const int m1 = k + 1 < nz ? k + 1 : 0;
-        double ut1, ub1, vt1, vb1, p1;
-        cell(m1, ut1, ub1, vt1, vb1, p1);
-        const double qzp = k + 1 < nzf ? Q[o + sxy] : (d.per[2] ? Q[col] : 0.0);
-        const double qxm = nbx.hm ? Q[o + nbx.m] : 0.0, qxp = nbx.hp ? Q[o + nbx.p] : 0.0;
-        const double qym = nby.hm ? Q[o + nby.m] : 0.0, qyp = nby.hp ? Q[o + nby.p] : 0.0;
-        const double lx = bx * q0 + ax * qxm + cx * qxp;
-        const double ly = by * q0 + ay * qym + cy * qyp;
-        const double lz = d.cb[2][k] * q0 + d.ca[2][k] * qzm + d.cc[2][k] * qzp;
-        const double li = (d.impl[0] ? lx : 0.0) + (d.impl[1] ? ly : 0.0) + (d.impl[2] ? lz : 0.0);
-        const double le = (d.impl[0] ? 0.0 : lx) + (d.impl[1] ? 0.0 : ly) + (d.impl[2] ? 0.0 : lz);
-        const double hz = d.h[2][k], w0 = d.w[2][k], w1 = d.w[2][m1];
-        const double ul = 0.5 * (qzm + q0), uh = 0.5 * (q0 + qzp);
-        double adv = -(uh * uh - ul * ul) / hz;
-        const double fxt = 0.5 * (w0 * ut0 + w1 * ut1), fxb = 0.5 * (w0 * ub0 + w1 * ub1);
-        adv -= (fxt * (0.5 * (q0 + qxp)) - fxb * (0.5 * (q0 + qxm))) / (hz * wx);
-        const double fyt = 0.5 * (w0 * vt0 + w1 * vt1), fyb = 0.5 * (w0 * vb0 + w1 * vb1);
-        adv -= (fyt * (0.5 * (q0 + qyp)) - fyb * (0.5 * (q0 + qym))) / (hz * wy);
-        const double gp = (p1 - p0) / hz;
-        const double ek = adv + d.nu * le;
-        double r = q0 + d.dt * (d.alpha * ek - d.gamma * gp) + d.cn * li;
-        if (d.use_prev) r += d.dt * d.beta * d.e[o];
-        d.e[o] = ek;
-        d.rhs[o] = r;
-        ut0 = ut1; ub0 = ub1; vt0 = vt1; vb0 = vb1; p0 = p1;
-        qzm = q0;
-        q0 = qzp;
+        // keep the offsets in 32 bits: as 64-bit loop invariants they cost a third resident block
+        asm("" : "+v"(u00), "+v"(um0), "+v"(up0), "+v"(u0m), "+v"(u0p), "+v"(ump), "+v"(v00), "+v"(v0m));
+        asm("" : "+v"(v0p), "+v"(vm0), "+v"(vp0), "+v"(vpm), "+v"(cm0), "+v"(cp0), "+v"(c0m), "+v"(c0p));
+        const bool hw = k < nwz, up = k + 1 < nz || d.per[2], wup = k + 1 < nwz || d.per[2];
+        // the plane above (wrapped; this plane again above a wall)
+        const long long ka = k + 1 < nz ? 1 : (d.per[2] ? 1 - nz : 0), kw = wup ? ka : 0;
+        const double* Ua = U + ka * uxy;
+        const double* Va = V + ka * vxy;
+        const double* Wk = hw ? W : W - pxy;   // (a plane that exists; zeroed below)
+        const double ua_ = Ua[u00], va_ = Va[v00], vla_ = Va[v0m], wa_ = (Wk + kw * pxy)[col], pa = P[ka * pxy + col];
+        const double uym_ = U[u0m], uyp_ = U[u0p], vyp_ = V[v0p], wym_ = Wk[c0m], wyp_ = Wk[c0p], pyp = P[c0p];
+        double lua = 0.0, luy = 0.0, lv = 0.0, lw = 0.0, ru = 0.0, rv = 0.0, rvl = 0.0, rw = 0.0, rp = 0.0;
+        if (edl) {
+            lua = Ua[um0];
+            luy = U[ump];
+            lv = V[vm0];
+            lw = Wk[cm0];
+        }
+        if (edr) {
+            ru = U[up0];
+            rv = V[vp0];
+            rvl = V[vpm];
+            rw = Wk[cp0];
+            rp = P[cp0];
+        }
+        const long long ou = (long long)k * uxy + u00, ov = (long long)k * vxy + v00, ow = (long long)k * pxy + col;
+        double eu = 0.0, ev = 0.0, ew = 0.0;
+        if (d.use_prev) {
+            eu = d.e[0][ou];
+            ev = d.e[1][ov];
+            if (hw) ew = d.e[2][ow];
+        }
+        const double ua = hu && up ? ua_ : 0.0, va = hv && up ? va_ : 0.0, vla = cym && up ? vla_ : 0.0, wa = wup ? wa_ : 0.0;
+        const double uym = cym ? uym_ : 0.0, uyp = hu && cyp ? uyp_ : 0.0, vyp = fyp ? vyp_ : 0.0;
+        const double wym = hw && cym ? wym_ : 0.0, wyp = hw && cyp ? wyp_ : 0.0;
+        auto left = [&](double q, double edge) {
+            const double x = lane_shift<DPP_WAVE_SHR1>(q);  // (with every lane of the wave)
+            return inl ? x : edge;
+        };
+        auto right = [&](double q, double edge) {
+            const double x = lane_shift<DPP_WAVE_SHL1>(q);  // (with every lane of the wave)
+            return inr ? x : edge;
+        };
+        const double ula = left(ua, up ? lua : 0.0), uly = left(uyp, luy), vxm = left(v, lv), wxm = left(w, hw ? lw : 0.0);
+        const double uxp = right(u, fxp ? ru : 0.0), vxp = right(v, hv ? rv : 0.0), vlx = right(vl, cym ? rvl : 0.0);
+        const double wxp = right(w, hw ? rw : 0.0), pxp = right(p, rp);
+        const double rwz = 1.0 / wz[k];
+        // transport of q by the fluxes fp, fm through the faces above and below
+        auto flux = [](double q, double qp, double qm, double fp, double fm) {
+            return fp * (0.5 * (q + qp)) - fm * (0.5 * (q + qm));
+        };
+        auto own = [](double q, double qp, double qm) {  // along the component's own direction
+            const double l = 0.5 * (qm + q), h = 0.5 * (q + qp);
+            return h * h - l * l;
+        };
+        auto mean = [](double w0, double q0, double w1, double q1) { return 0.5 * (w0 * q0 + w1 * q1); };
+        auto put = [&](int c, long long o, double q, double adv, double li, double le, double gp, double e) {
+            const double ek = d.nu * le - adv;
+            double r = q + d.dt * (d.alpha * ek - d.gamma * gp) + d.cn * li;
+            if (d.use_prev) r += d.dt * d.beta * e;
+            d.e[c][o] = ek;
+            d.rhs[c][o] = r;
+        };
+        double li, le;
+        if (hu) {
+            ns_diffusion<NI>(rfx(ul, u, uxp), rcy(uym, u, uyp), zrow(0, k)(ub, u, ua), li, le);
+            const double ft = mean(wx0, v, wx1, vxp), fb = mean(wx0, vl, wx1, vlx);
+            const double gt = mean(wx0, w, wx1, wxp), gb = mean(wx0, wb, wx1, wbx);
+            const double adv = (own(u, uxp, ul) + flux(u, uyp, uym, ft, fb) * rwy + flux(u, ua, ub, gt, gb) * rwz) * rhx;
+            put(0, ou, u, adv, li, le, (pxp - p) * rhx, eu);
+        }
+        if (hv) {
+            ns_diffusion<NI>(rcx(vxm, v, vxp), rfy(vl, v, vyp), zrow(0, k)(vb, v, va), li, le);
+            const double ft = mean(wy0, u, wy1, uyp), fb = mean(wy0, ul, wy1, uly);
+            const double gt = mean(wy0, w, wy1, wyp), gb = mean(wy0, wb, wy1, wby);
+            const double adv = (own(v, vyp, vl) + flux(v, vxp, vxm, ft, fb) * rwx + flux(v, va, vb, gt, gb) * rwz) * rhy;
+            put(1, ov, v, adv, li, le, (pyp - p) * rhy, ev);
+        }
+        if (hw) {
+            const double rhz = 1.0 / hz[k], w0 = wz[k], w1 = wz[k + 1 < nz ? k + 1 : 0];
+            ns_diffusion<NI>(rcx(wxm, w, wxp), rcy(wym, w, wyp), zrow(1, k)(wb, w, wa), li, le);
+            const double ft = mean(w0, u, w1, ua), fb = mean(w0, ul, w1, ula);
+            const double gt = mean(w0, v, w1, va), gb = mean(w0, vl, w1, vla);
+            const double adv = (own(w, wa, wb) + flux(w, wxp, wxm, ft, fb) * rwx + flux(w, wyp, wym, gt, gb) * rwy) * rhz;
+            put(2, ow, w, adv, li, le, (pa - p) * rhz, ew);
+        }
+        ub = u;
+        vb = v;
+        wb = w;
+        wbx = wxp;
+        wby = wyp;
+        u = ua;
+        ul = ula;
+        v = va;
+        vl = vla;
+        w = wa;
+        p = pa;
+        U += uxy;
+        V += vxy;
+        W += pxy;
+        P += pxy;
     }
 }
 
@@ -256,16 +284,17 @@ inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 }  // namespace
 
-hipError_t launch_ns_explicit(int comp, const NsDesc& d, hipStream_t s) {
-    const long long ncol = comp == 0 ? (long long)d.nf[0] * d.N[1]
-                         : comp == 1 ? (long long)d.N[0] * d.nf[1] : (long long)d.N[0] * d.N[1];
-    const int planes = comp == 2 ? d.nf[2] : d.N[2];
-    const long long nb = ns_blocks(ncol, planes);
+hipError_t launch_ns_explicit(NsDesc d, int nimpl, hipStream_t s) {
+    const long long ncb = ((long long)d.N[0] * d.N[1] + NS_NT - 1) / NS_NT;
+    d.rz = ns_chunk(ncb, d.N[2]);
+    const long long nb = ncb * ((d.N[2] + d.rz - 1) / d.rz);
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (comp == 0) TPT_KLAUNCH(ns_explicit_xy_kernel<0>, dim3((unsigned)nb), dim3(NS_NT), 0, s, d);
-    else if (comp == 1) TPT_KLAUNCH(ns_explicit_xy_kernel<1>, dim3((unsigned)nb), dim3(NS_NT), 0, s, d);
-    else TPT_KLAUNCH(ns_explicit_z_kernel, dim3((unsigned)nb), dim3(NS_NT), 0, s, d);
+    const dim3 grid((unsigned)nb), block(NS_NT);
+    if (nimpl == 0) TPT_KLAUNCH(ns_explicit_kernel<0>, grid, block, 0, s, d);
+    else if (nimpl == 1) TPT_KLAUNCH(ns_explicit_kernel<1>, grid, block, 0, s, d);
+    else if (nimpl == 2) TPT_KLAUNCH(ns_explicit_kernel<2>, grid, block, 0, s, d);
+    else TPT_KLAUNCH(ns_explicit_kernel<3>, grid, block, 0, s, d);
     return hipGetLastError();
 }
 
@@ -451,33 +480,34 @@ int tpt_ns_substep(tpt_ns ns, int k, double* u, double* v, double* w, double* eu
     // explicit terms and the right-hand sides of the three components (all
     // read u^k, so the velocity is overwritten only after the last one)
     const tpt_plan_s* pp = ns->pressure;
-    static const char* names[3] = {"ns_explicit_u", "ns_explicit_v", "ns_explicit_w"};
-    for (int c = 0; c < 3; ++c) {
-        NsDesc d{};
-        for (int e = 0; e < 3; ++e) {
-            d.N[e] = ns->N[e];
-            d.nf[e] = ns->nf[e];
-            d.per[e] = ns->per[e];
-            d.impl[e] = ns->impl[e];
-            d.ca[e] = ns->ca[c][e];
-            d.cb[e] = ns->cb[c][e];
-            d.cc[e] = ns->cc[c][e];
-            d.q[e] = vel[e];
+    NsDesc nd{};
+    for (int e = 0; e < 3; ++e) {
+        nd.N[e] = ns->N[e];
+        nd.nf[e] = ns->nf[e];
+        nd.per[e] = ns->per[e];
+        for (int f = 0; f < 2; ++f) {  // the other components are cell-located along e, with one operator
+            const int c = f ? e : (e + 1) % 3;
+            nd.ca[f][e] = ns->ca[c][e];
+            nd.cb[f][e] = ns->cb[c][e];
+            nd.cc[f][e] = ns->cc[c][e];
         }
-        d.w[0] = pp->buf.vx; d.w[1] = pp->buf.vy; d.w[2] = pp->buf.vz;
-        d.h[0] = pp->buf.dcx; d.h[1] = pp->buf.dcy; d.h[2] = pp->buf.dcz;
-        d.P = p;
-        d.e = ex[c];
-        d.rhs = rhs[c];
-        d.dt = ns->dt;
-        d.nu = ns->nu;
-        d.alpha = alpha;
-        d.beta = beta;
-        d.gamma = gamma;
-        d.cn = cn;
-        d.use_prev = k > 1 ? 1 : 0;
-        TimedScope ts(names[c], s);
-        hipError_t e = launch_ns_explicit(c, d, s);
+        nd.q[e] = vel[e];
+        nd.e[e] = ex[e];
+        nd.rhs[e] = rhs[e];
+    }
+    nd.w[0] = pp->buf.vx; nd.w[1] = pp->buf.vy; nd.w[2] = pp->buf.vz;
+    nd.h[0] = pp->buf.dcx; nd.h[1] = pp->buf.dcy; nd.h[2] = pp->buf.dcz;
+    nd.P = p;
+    nd.dt = ns->dt;
+    nd.nu = ns->nu;
+    nd.alpha = alpha;
+    nd.beta = beta;
+    nd.gamma = gamma;
+    nd.cn = cn;
+    nd.use_prev = k > 1 ? 1 : 0;
+    {
+        TimedScope ts("ns_explicit", s);
+        hipError_t e = launch_ns_explicit(nd, ns->impl[0] + ns->impl[1] + ns->impl[2], s);
         if (e != hipSuccess) return fail(TPT_ERR_HIP, std::string("NS explicit launch: ") + hipGetErrorString(e));
     }
     // implicit diffusion: (I - c L_I) u* = rhs, u* into the velocity arrays
