@@ -228,7 +228,14 @@ struct ThomasDesc {
 // per line, one lane per segment, LB lines per block) in one of THOMAS_NPART
 // configurations; THOMAS_CYC + configuration for cyclic lines, which the
 // automatic choice alone selects.
-enum { THOMAS_AUTO = 0, THOMAS_SEQ = 1, THOMAS_PART = 2, THOMAS_NPART = 17, THOMAS_CYC = THOMAS_PART + THOMAS_NPART };
+enum {
+    THOMAS_AUTO = 0,
+    THOMAS_SEQ = 1,
+    THOMAS_PART = 2,
+    THOMAS_NPART = 27,
+    THOMAS_NAPI = 17,  // configurations that can be asked for
+    THOMAS_CYC = THOMAS_PART + THOMAS_NPART
+};
 inline int thomas_config(int variant) { return variant - (variant >= THOMAS_CYC ? THOMAS_CYC : THOMAS_PART); }
 // the variant launch_thomas runs for t (-1: t.variant does not fit t)
 int thomas_variant(const ThomasDesc& t);

@@ -706,8 +706,10 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
             }
             if (best >= 0) autotune_record(prec, kind, g.M, g.N, g.K, best);
         }
-        // Thomas kernel: the sequential one and every partitioned
-        // configuration that fits, on the plan's own lines (one system)
+        // Thomas kernel: the automatic choice, the sequential one and every
+        // partitioned configuration of a number that fits, on the plan's own
+        // lines (one system); nothing to record where the automatic choice
+        // has no number and is the fastest
         if (!p->op[2].periodic && !p->seq_thomas) {
             const int dt = prec == GP_F64 ? DT_F64 : DT_F32;
             const long long lines = (long long)p->N[0] * p->N[1];
@@ -719,7 +721,10 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
                 ThomasDesc t = plan_thomas(p, in, dt, outb, dt, (double*)scratch, 1);
                 int best = -1;
                 float best_ms = 1e30f;
+                t.variant = THOMAS_AUTO;
+                const int chosen = thomas_variant(t);
                 for (int v = THOMAS_SEQ; v < THOMAS_PART + THOMAS_NPART; ++v) {
+                    if (v >= THOMAS_PART + THOMAS_NAPI && v != chosen) continue;
                     t.variant = v;
                     if (thomas_variant(t) != v || launch_thomas(t, s) != hipSuccess) continue;  // warm-up
                     float ms_min = 1e30f;
@@ -737,7 +742,7 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
                         best = v;
                     }
                 }
-                if (best >= 0) autotune_record(prec, TUNE_THOMAS, (int)lines, p->N[2], 0, best);
+                if (best >= 0 && best < THOMAS_PART + THOMAS_NAPI) autotune_record(prec, TUNE_THOMAS, (int)lines, p->N[2], 0, best);
                 (void)hipStreamSynchronize(s);
                 (void)hipFree(scratch);
             } else {

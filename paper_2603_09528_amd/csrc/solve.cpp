@@ -780,7 +780,7 @@ int tpt_thomas(int nx, int ny, int nz, int nsys, const double* lamx, const doubl
                const double* bz, const double* cz, int periodic_z, double sigma, double tau, int pin_line,
                const double* f, double* x, double* scratch, int variant, void* stream) {
     if (nx < 1 || ny < 1 || nz < 1 || nsys < 1) return fail(TPT_ERR_INVALID, "bad sizes");
-    if (variant < -1 || variant > THOMAS_NPART) return fail(TPT_ERR_INVALID, "bad Thomas variant");
+    if (variant < -1 || variant > THOMAS_NAPI) return fail(TPT_ERR_INVALID, "bad Thomas variant");
     if (periodic_z && nz < 2) return fail(TPT_ERR_INVALID, "cyclic lines need nz >= 2");
     if (!lamx || !lamy || !az || !bz || !cz || !f || !x || !scratch) return fail(TPT_ERR_INVALID, "NULL pointer");
     if (pin_line >= nx * ny) return fail(TPT_ERR_INVALID, "pin_line out of range");
@@ -917,7 +917,7 @@ int tpt_autotune_load(const char* path) {
         int prec, kind, M, N, K, v;
         if (!(is >> prec >> kind >> M >> N >> K >> v)) continue;
         if (prec < GP_F64 || prec > GP_BF16X3 || kind < 0 || kind > TUNE_THOMAS) continue;
-        if (kind == TUNE_THOMAS ? (v < THOMAS_SEQ || v >= THOMAS_PART + THOMAS_NPART) : (v < 0 || v >= TV_COUNT))
+        if (kind == TUNE_THOMAS ? (v < THOMAS_SEQ || v >= THOMAS_PART + THOMAS_NAPI) : (v < 0 || v >= TV_COUNT))
             continue;
         g_tune[tune_key(prec, kind, M, N, K)] = v;
     }

@@ -369,27 +369,39 @@ __global__ __launch_bounds__(LB * P) void thomas_part_multi_kernel(const ThomasD
 // line of nz planes needs P L >= nz.  Blocks of LB P lanes; the register
 // count grows with L (about 122 at L = 16, 246 at L = 32), which with the
 // block size sets how many blocks share a compute unit.
+// The first THOMAS_NAPI are also reached by number (tpt_thomas, the autotuner's
+// table), the others by the automatic choice alone.
 struct ThomasPart {
     int LB, P, L;
 };
 #define TPT_THOMAS_PARTS(X) \
-    X(64, 4, 8)             \
-    X(64, 8, 8)             \
-    X(32, 8, 8)             \
-    X(64, 8, 16)            \
-    X(32, 8, 16)            \
-    X(16, 8, 16)            \
-    X(64, 16, 16)           \
-    X(32, 16, 16)           \
-    X(16, 16, 16)           \
-    X(64, 8, 32)            \
-    X(32, 8, 32)            \
-    X(16, 8, 32)            \
-    X(16, 32, 16)           \
-    X(32, 16, 32)           \
-    X(16, 16, 32)           \
-    X(16, 64, 16)           \
-    X(16, 32, 32)
+    X(64, 4, 8) \
+    X(64, 8, 8) \
+    X(32, 8, 8) \
+    X(64, 8, 16) \
+    X(32, 8, 16) \
+    X(16, 8, 16) \
+    X(64, 16, 16) \
+    X(32, 16, 16) \
+    X(16, 16, 16) \
+    X(64, 8, 32) \
+    X(32, 8, 32) \
+    X(16, 8, 32) \
+    X(16, 32, 16) \
+    X(32, 16, 32) \
+    X(16, 16, 32) \
+    X(16, 64, 16) \
+    X(16, 32, 32) \
+    X(32, 8, 12) \
+    X(32, 8, 20) \
+    X(32, 8, 24) \
+    X(32, 16, 12) \
+    X(16, 16, 20) \
+    X(32, 16, 20) \
+    X(16, 16, 24) \
+    X(32, 16, 24) \
+    X(16, 32, 20) \
+    X(16, 32, 24)
 #define TPT_TP_ROW(XLB, XP, XL) {XLB, XP, XL},
 constexpr ThomasPart THOMAS_PARTS[] = {TPT_THOMAS_PARTS(TPT_TP_ROW)};
 #undef TPT_TP_ROW
@@ -401,23 +413,53 @@ void thomas_part_shape(int v, int* lb, int* p, int* l) {
     *l = THOMAS_PARTS[v].L;
 }
 
-// Automatic choice by nz and line count (the autotuner's measurement on the
-// plan's own lines takes precedence): the configuration measured fastest on
-// lines of 32, 64, 128, 256, 512 and 1024 planes (FP64, 16 K - 1 M lines).
-// Small blocks win: with the barriers of each block, several blocks per
-// compute unit keep its loads going while one block computes; from about
-// 256 K lines, 32-line blocks (256-byte plane segments) overtake 16-line ones
-// (1024^2 x 256: 0.98 against 1.22 ms; 256^3: 55 against 54 us).  Lines of
-// more than 512 planes need 1024-lane blocks (one per compute unit); with
-// many lines the sequential kernel then has parallelism enough and is faster
-// (1024^3: 5.2 against 6.9 ms), with few it is not (32 K lines of 1024
-// planes: 0.24 against 0.17 ms).
-static int thomas_part_auto(int nz, long long lines) {
-    if (nz > 512 && lines >= 131072) return -1;
-    const bool many = lines >= 262144;
-    const int want[][2] = {{32, 0}, {64, 2}, {128, 4}, {256, many ? 7 : 8}, {512, many ? 13 : 12}, {1024, 15}};
-    for (const auto& w : want)
-        if (nz <= w[0]) return w[1];
+static int part_index(int lb, int p, int l) {
+    for (int v = 0; v < THOMAS_NPART; ++v)
+        if (THOMAS_PARTS[v].LB == lb && THOMAS_PARTS[v].P == p && THOMAS_PARTS[v].L == l) return v;
+    return -1;
+}
+
+// Automatic choice by nz, line count, storage type and boundary (the
+// autotuner's measurement on the plan's own lines takes precedence): the
+// configuration measured fastest on 16 K to 1 M lines.
+// - Rows past nz cost as much as others, so P L follows nz in steps of an
+//   eighth to a third: 262 144 lines, FP64, of 160 planes 112 us in segments
+//   of 20 against 180 in 16 x 16; of 320 planes 313 against 478 in 16 x 32;
+//   FP32, 223 against 412.
+// - Small blocks win: with the barriers of each block, several blocks per
+//   compute unit keep its loads going while one block computes; with many
+//   lines 32-line blocks (256-byte plane segments) overtake 16-line ones
+//   (1024^2 x 256: 0.93 against 1.13 ms; 102 400 lines of 256: 88 against 90
+//   us, cyclic 84 against 97; 65 536 cyclic lines 60 against 56).  FP32 lines of 256 planes take them always (128-byte segments:
+//   102 400 lines, 59 against 62 us).
+// - Lines of more than 512 planes have blocks of 512 lanes and more.  With
+//   very many lines the sequential kernel then has parallelism enough and is
+//   faster (1024^3: 5.6 against 7.0 ms; 262 144 lines of 1024: 1.46 against
+//   1.42; of 640, 0.86 against 0.85; FP32, where it moves fewer bytes, 102 400
+//   lines of 640: 216 against 248 us, 40 000: 145 against 84; 1 M lines of 512:
+//   1.51 against 1.76 ms).  Cyclic lines stay partitioned (262 144 lines of
+//   1024: 1.56 against 2.15 ms).
+static int thomas_part_auto(int nz, long long lines, bool f32, bool cyc) {
+    if (!cyc) {
+        if (nz > 512 && lines >= (f32 ? 98304 : 524288)) return -1;
+        if (f32 && nz > 384 && lines >= 524288) return -1;
+    }
+    const bool many = lines >= 262144, wide = lines >= 98304;
+    if (nz <= 32) return part_index(64, 4, 8);
+    if (nz <= 64) return part_index(32, 8, 8);
+    if (nz <= 96) return part_index(32, 8, 12);
+    if (nz <= 128) return part_index(32, 8, 16);
+    if (nz <= 160) return part_index(32, 8, 20);
+    if (nz <= 192) return f32 ? part_index(32, 8, 24) : part_index(32, 16, 12);
+    if (nz <= 256) return f32 || wide ? part_index(32, 16, 16) : part_index(16, 16, 16);
+    // (102 400 cyclic lines of 320: 100 us in 32-line blocks, 110 in 16-line
+    // ones; plain ones 123 and 105)
+    if (nz <= 320) return (cyc ? f32 || wide : !f32 && many) ? part_index(32, 16, 20) : part_index(16, 16, 20);
+    if (nz <= 384) return !cyc && !f32 && many ? part_index(32, 16, 24) : part_index(16, 16, 24);
+    if (nz <= 512) return !f32 && many ? part_index(32, 16, 32) : part_index(16, 32, 16);
+    if (nz <= 640) return part_index(16, 32, 20);
+    if (nz <= 768) return part_index(16, 32, 24);
+    if (nz <= 1024) return part_index(16, 64, 16);
     return -1;
 }
 
@@ -426,7 +468,7 @@ int thomas_variant(const ThomasDesc& t) {
     if (t.variant == THOMAS_SEQ) return THOMAS_SEQ;
     if (t.variant == THOMAS_AUTO) {
         if (!same || t.nz < 16) return THOMAS_SEQ;
-        const int v = thomas_part_auto(t.nz, (long long)t.nx * t.ny * t.nsys);
+        const int v = thomas_part_auto(t.nz, (long long)t.nx * t.ny * t.nsys, t.tf == DT_F32, t.periodic);
         // cyclic lines in the same configuration; its segments have at least
         // two rows (nz >= 2 P) by the table's choice of P
         return v < 0 ? THOMAS_SEQ : (t.periodic ? THOMAS_CYC : THOMAS_PART) + v;
@@ -448,13 +490,22 @@ long long thomas_part_blocks(const ThomasDesc& t, int v) {
 
 // Configurations compiled for cyclic lines: those of the automatic choice.
 #define TPT_THOMAS_CYC(X) \
-    X(64, 4, 8)           \
-    X(32, 8, 8)           \
-    X(32, 8, 16)          \
-    X(32, 16, 16)         \
-    X(16, 16, 16)         \
-    X(16, 32, 16)         \
-    X(32, 16, 32)         \
+    X(64, 4, 8) \
+    X(32, 8, 8) \
+    X(32, 8, 12) \
+    X(32, 8, 16) \
+    X(32, 8, 20) \
+    X(32, 8, 24) \
+    X(32, 16, 12) \
+    X(32, 16, 16) \
+    X(16, 16, 16) \
+    X(16, 16, 20) \
+    X(32, 16, 20) \
+    X(16, 16, 24) \
+    X(16, 32, 16) \
+    X(32, 16, 32) \
+    X(16, 32, 20) \
+    X(16, 32, 24) \
     X(16, 64, 16)
 
 template <typename T>
