@@ -23,7 +23,9 @@ struct SyncWave {
     }
 };
 
-__device__ __forceinline__ int pad16(int c) { return c + (c >> 4); }
+// (for a and b without common bits pad16(a + b) = pad16(a) + pad16(b): the
+// passes write it so, which leaves an address and constant offsets)
+__host__ __device__ constexpr int pad16(int c) { return c + (c >> 4); }
 __device__ __forceinline__ int bitrev(int v, int bits) { return bits ? (int)(__brev((unsigned)v) >> (32 - bits)) : 0; }
 __host__ __device__ constexpr int brev_c(int v, int bits) {
     int r = 0;
@@ -106,7 +108,7 @@ __device__ __forceinline__ void ut_pass0(double2* a, int t, int T, int mlog, con
 #pragma unroll
         for (int j = 0; j < P0; ++j) {
             const int n = g + j * G0;
-            x[r * P0 + brev_c(j, Q0)] = INV ? ut_fold(a, n, M, W) : a[pad16(n)];
+            x[r * P0 + brev_c(j, Q0)] = INV ? ut_fold(a, n, M, W) : a[pad16(g) + pad16(j * G0)];
         }
     }
     SY::sync();
@@ -115,7 +117,7 @@ __device__ __forceinline__ void ut_pass0(double2* a, int t, int T, int mlog, con
         dit_regs<Q0, INV>(x + r * P0);
         const int base = bitrev(t + r * T, mlog - Q0) << Q0;
 #pragma unroll
-        for (int j = 0; j < P0; ++j) a[pad16(base + j)] = x[r * P0 + j];
+        for (int j = 0; j < P0; ++j) a[pad16(base) + j] = x[r * P0 + j];
     }
     SY::sync();
 }
@@ -142,12 +144,12 @@ __device__ __forceinline__ void ut_passk(double2* a, int t, int mlog, int h, con
         }
     double2 x[P];
 #pragma unroll
-    for (int k = 0; k < P; ++k) x[k] = a[pad16(base + (k << h))];
+    for (int k = 0; k < P; ++k) x[k] = a[pad16(base) + pad16(k << h)];
 #pragma unroll
     for (int k = 1; k < P; ++k) x[k] = cmul(x[k], tw[brev_c(k, Q)]);
     dit_regs<Q, INV>(x);
 #pragma unroll
-    for (int j = 0; j < P; ++j) a[pad16(base + (j << h))] = x[j];
+    for (int j = 0; j < P; ++j) a[pad16(base) + pad16(j << h)] = x[j];
     SY::sync();
 }
 
@@ -156,9 +158,10 @@ __device__ __forceinline__ void ut_passk(double2* a, int t, int mlog, int h, con
 // (one thread for M <= 2^QM), each holding up to 2^QM points per pass.  Every
 // thread of the synchronisation group SY takes part (the passes hold its
 // barriers); INV folds the half spectrum on the first read and uses
-// conjugate twiddles.
-template <int QM, bool INV, class SY>
-__device__ __forceinline__ void ut_cfft_line(double2* a, int t, int mlog, const double2* W) {
+// conjugate twiddles.  ML: mlog where it is known when compiled.
+template <int QM, bool INV, class SY, int ML = 0>
+__device__ __forceinline__ void ut_cfft_line(double2* a, int t, int mlog_, const double2* W) {
+    const int mlog = ML ? ML : mlog_;
     const int Q = mlog < QM ? mlog : QM;
     const int T = 1 << (mlog - Q);
     const int npass = (mlog + Q - 1) / Q, q0 = mlog - (npass - 1) * Q;
@@ -171,7 +174,12 @@ __device__ __forceinline__ void ut_cfft_line(double2* a, int t, int mlog, const 
     else if constexpr (QM == 3) ut_pass0<QM, 3, INV, SY>(a, t, T, mlog, W);
     else if (q0 == 3) ut_pass0<QM, 3, INV, SY>(a, t, T, mlog, W);
     else ut_pass0<QM, 4, INV, SY>(a, t, T, mlog, W);
-    for (int h = q0; h < mlog; h += QM) ut_passk<QM, INV, SY>(a, t, mlog, h, W);
+    if constexpr (ML > 0) {
+#pragma unroll
+        for (int h = q0; h < mlog; h += QM) ut_passk<QM, INV, SY>(a, t, mlog, h, W);
+    } else {
+        for (int h = q0; h < mlog; h += QM) ut_passk<QM, INV, SY>(a, t, mlog, h, W);
+    }
 }
 
 }  // namespace fftc

@@ -197,7 +197,10 @@ struct FftDesc {
 bool fft_supported(int n);
 long long fft_blocks(const FftDesc& d);
 int fft_lines_per_block(int n);
-hipError_t launch_fft(const FftDesc& rep, const FftDesc* d_work, int nwork, long long blocks, hipStream_t s);
+hipError_t launch_fft(const FftDesc& d, long long blocks, hipStream_t s);
+// rep: a representative descriptor; every descriptor of the list has its types,
+// direction, epilogue and line length
+hipError_t launch_fft_multi(const FftDesc& rep, const FftDesc* d_work, int nwork, long long blocks, hipStream_t s);
 
 // y GEMM of one problem (descriptor of the y pass) whose B rows are first
 // transformed along x (descriptor of the x pass: kind, direction, scale,

@@ -505,7 +505,7 @@ int MultiExec::enqueue(hipStream_t s) const {
             case 4: {
                 TimedScope ts("multi_fft", s);
                 const FftDesc& rep = *(const FftDesc*)(blob_.data() + L.off);
-                e = launch_fft(rep, (const FftDesc*)(d_desc_ + L.off), L.nwork, L.total, s);
+                e = launch_fft_multi(rep, (const FftDesc*)(d_desc_ + L.off), L.nwork, L.total, s);
                 break;
             }
         }

@@ -387,7 +387,7 @@ static int run_stage(const tpt_plan_s* p, int stage, int prec, const void* in, i
     const long long nb = fft_blocks(f);
     if (nblocks) *nblocks = nb;
     TimedScope ts(fast_name(stage, tin, tout), s);
-    hipError_t e = launch_fft(f, nullptr, 0, nb, s);
+    hipError_t e = launch_fft(f, nb, s);
     if (e != hipSuccess) return fail(TPT_ERR_HIP, std::string("fast transform launch: ") + hipGetErrorString(e));
     return TPT_OK;
 }
