@@ -19,7 +19,7 @@ bool fold_fits(int n, int nx, bool ylines, int prec) {
 static void fold_dims(const FoldDesc& g, int shape, int* ph, int* dn) {
     *ph = shape == FOLD_64x128 ? 64 : shape == FOLD_32x128 ? 32 : 16;
     if (g.prec == GP_BF16X3) *dn = shape == FOLD_64x128 ? 128 : 64;
-    else *dn = shape == FOLD_16x64 || (shape == FOLD_64x128 && g.X) ? 64 : 128;
+    else *dn = shape == FOLD_16x64 || (shape == FOLD_64x128 && g.corr) ? 64 : 128;
 }
 
 long long fold_tiles(FoldDesc& g, int shape) {
@@ -43,7 +43,7 @@ static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
     static const double rate[3][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.92, 0.55}, {1.0, 0.7, 0.0}};
     int ph, dn;
     fold_dims(g, shape, &ph, &dn);
-    return (double)((tiles + 255) / 256) * ph * dn / rate[g.prec == GP_BF16X3 ? 2 : g.X ? 1 : 0][shape];
+    return (double)((tiles + 255) / 256) * ph * dn / rate[g.prec == GP_BF16X3 ? 2 : g.corr][shape];
 }
 
 int fold_shape(const FoldDesc* g, int count) {
@@ -65,7 +65,7 @@ int fold_shape(const FoldDesc* g, int count) {
 }
 
 long long fold_grid(const FoldDesc& g, int shape, long long total) {
-    long long percu = shape == FOLD_64x128 || (shape == FOLD_32x128 && g.X) ? 2 : shape == FOLD_32x128 ? 3 : 5;
+    long long percu = shape == FOLD_64x128 || (shape == FOLD_32x128 && g.corr) ? 2 : shape == FOLD_32x128 ? 3 : 5;
     if (g.prec == GP_BF16X3 && shape == FOLD_32x128) percu = 4;
     return std::min(total, 256 * percu);
 }
@@ -109,7 +109,7 @@ static hipError_t launch_f64(const FoldDesc& g, const FoldList* list, long long 
 
 hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s) {
     if (g.tin != DT_F64 || g.tout != DT_F64 || g.epi != EPI_STORE) return hipErrorInvalidValue;
-    return g.X ? launch_f64<true>(g, list, total, shape, s)
+    return g.corr ? launch_f64<true>(g, list, total, shape, s)
                : launch_f64<false>(g, list, total, shape, s);
 }
 

@@ -53,6 +53,7 @@ struct DirBasis {
     uint16_t* fx_qinv = nullptr;
     uint16_t* fx_q = nullptr;
     double2* f_rot = nullptr;
+    int f_corr = 0;                  // fx and f_rot are not trivial
     int hp = 0, kp = 0;
     // BF_DENSE
     double* d_qinv = nullptr;        // FP64

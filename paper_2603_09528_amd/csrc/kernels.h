@@ -109,9 +109,9 @@ hipError_t launch_gemm_bf16(const GemmDesc& g, const GemmDesc* d_work, int nwork
 // fold_impl.h): every line of the direction, x lines contiguous, y lines the
 // columns of each z slab (column c = slab * inner + i).  P holds the padded
 // even and odd bases by K step, in the compute type or as BF16 hi and lo
-// planes; the modes of a line
-// are kept even ones first.  X and rot: the remainders and rotations of a
-// basis that is symmetric only up to rounding (FP64), or null.
+// planes; the modes of a line are kept even ones first.  X and rot (FP64): the
+// remainders and rotations of a basis that is symmetric only up to rounding
+// (corr; zero and trivial for an exactly symmetric one).
 struct FoldDesc {
     const void* P;
     const uint16_t* X;
@@ -121,6 +121,7 @@ struct FoldDesc {
     int n, h;               // line length and (n + 1) / 2
     int hp, kp;             // h rounded up to FOLD_ROWS and fold_cols(prec)
     int prec;               // GemmPrec
+    int corr;               // apply X and rot
     int ylines, inverse;
     int inner;              // y lines: Nx
     long long lines;        // x: Ny Nz nrhs; y: Nx Nz nrhs

@@ -155,17 +155,33 @@ int MultiExec::add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& 
     return TPT_OK;
 }
 
+// Tiles (of 32 x 128) up to which one kind of half-size products joins the
+// launch of the other: 16 uneven problems of 24 to 192 cells a direction 1100
+// us a batch apart, 1095 up to 512 tiles, 1074 up to 2048; ten requests of 64
+// to 224, 2240, 2230, 2216, and 2370 always together.
+constexpr long long FOLD_MERGE = 2048;
+
 int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const std::vector<char>& use,
                               std::vector<long long>* nb) {
     // one persistent launch for the problems with remainders and one for the
-    // others; every tile shape gives the same bits, so batch and single results
-    // agree whatever shapes they take
-    for (int corr = 0; corr < 2; ++corr) {
+    // others; a few tiles join the others' launch instead (their remainders are
+    // zero: 13 % more time a tile at 256^3, against a launch of its own with
+    // most of the device idle).  Every tile shape gives the same bits, and so do
+    // zero remainders, so batch and single results agree.
+    long long tiles[2] = {0, 0};
+    for (size_t i = 0; i < gs.size(); ++i)
+        if (use[i]) {
+            FoldDesc g = gs[i];
+            tiles[g.corr] += fold_tiles(g, FOLD_32x128);
+        }
+    const bool merge = tiles[0] > 0 && tiles[1] > 0 && std::min(tiles[0], tiles[1]) <= FOLD_MERGE;
+    for (int corr = merge ? 1 : 0; corr < 2; ++corr) {
         std::vector<FoldDesc> grp;
         std::vector<size_t> idx;
         for (size_t i = 0; i < gs.size(); ++i) {
-            if (!use[i] || (gs[i].X != nullptr) != (corr == 1)) continue;
+            if (!use[i] || (!merge && gs[i].corr != corr)) continue;
             grp.push_back(gs[i]);
+            grp.back().corr = corr;
             idx.push_back(i);
         }
         if (grp.empty()) continue;

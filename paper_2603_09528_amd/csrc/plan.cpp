@@ -128,11 +128,10 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             o_tw = take(16 * (size_t)(n / 2));
             o_qtw = take(16 * (size_t)(n / 2 + 1));
         } else if (form == BF_FOLD) {
-            if (prec != GP_F64) fb.rotated = false;
             const size_t es = prec == GP_F64 ? 8 : 4;  // (two bf16 planes: 4 bytes)
             o_qinv = take(es * nf);
             o_q = take(es * nf);
-            if (fb.rotated) {
+            if (prec == GP_F64) {
                 o_xqinv = take(2 * nf);
                 o_xq = take(2 * nf);
                 o_rot = take(8 * fb.rot.size());
@@ -200,7 +199,7 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
                     bq[o + (size_t)hp * 32] = host_bf16((float)(fb.inv[e] - (double)host_bf16_to_f(hj)));
                 }
             }
-            if (fb.rotated) {
+            if (prec == GP_F64) {
                 uint16_t* xi = (uint16_t*)(host.data() + o_xqinv);
                 uint16_t* xq = (uint16_t*)(host.data() + o_xq);
                 for (size_t e = 0; e < nf; ++e) {
@@ -270,7 +269,8 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
                 b->fb_qinv = (uint16_t*)(d + o_qinv);
                 b->fb_q = (uint16_t*)(d + o_q);
             }
-            if (fb.rotated) {
+            if (prec == GP_F64) {
+                b->f_corr = fb.rotated ? 1 : 0;
                 b->fx_qinv = (uint16_t*)(d + o_xqinv);
                 b->fx_q = (uint16_t*)(d + o_xq);
                 b->f_rot = (double2*)(d + o_rot);

@@ -215,6 +215,7 @@ FoldDesc stage_fold(const tpt_plan_s* p, int stage, const void* in, int tin, voi
         g.P = fwd ? b->fd_qinv : b->fd_q;
         g.X = fwd ? b->fx_qinv : b->fx_q;
         g.rot = b->f_rot;
+        g.corr = b->f_corr;
     } else g.P = fwd ? b->fs_qinv : b->fs_q;
     g.in = in;
     g.out = out;
