@@ -429,7 +429,7 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
     return TPT_OK;
 }
 
-int MultiExec::upload(void* d_desc, hipStream_t s) {
+int MultiExec::upload(void* d_desc, hipStream_t s, bool wait) {
     d_desc_ = (char*)d_desc;
     if (blob_.empty()) return TPT_OK;
     if (pinned_bytes_ < blob_.size()) {
@@ -441,7 +441,7 @@ int MultiExec::upload(void* d_desc, hipStream_t s) {
     }
     std::memcpy(pinned_, blob_.data(), blob_.size());
     TPT_HIP(hipMemcpyAsync(d_desc, pinned_, blob_.size(), hipMemcpyHostToDevice, s));
-    TPT_HIP(hipStreamSynchronize(s));
+    if (wait) TPT_HIP(hipStreamSynchronize(s));
     return TPT_OK;
 }
 

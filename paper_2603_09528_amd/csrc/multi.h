@@ -21,7 +21,9 @@ class MultiExec {
     // desc_bytes() bytes of device memory (uploaded by upload()).
     int build(const double* const* rhs, double* const* out, void* ws);
     size_t desc_bytes() const { return blob_.size(); }
-    int upload(void* d_desc, hipStream_t s);  // async copy of the blob (pinned staging)
+    // copy of the blob (pinned staging); not waited for if the caller uploads
+    // again only after the stream has passed it
+    int upload(void* d_desc, hipStream_t s, bool wait = true);
     // Enqueue every launch on s (graph-capturable: kernels only).
     int enqueue(hipStream_t s) const;
     int count() const { return (int)plans_.size(); }

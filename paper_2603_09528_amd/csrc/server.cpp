@@ -13,6 +13,8 @@
 #include <deque>
 #include <thread>
 
+#include <sys/prctl.h>
+
 #include "multi.h"
 
 namespace tpt {
@@ -233,7 +235,8 @@ bool tpt_server_s::admit_locked() {
                 s.d_desc_bytes = s.exec.desc_bytes();
             }
         }
-        if (rc == TPT_OK) rc = s.exec.upload(s.d_desc, s.stream);
+        // (the slot's staging is free again: it waits for its last group's event)
+        if (rc == TPT_OK) rc = s.exec.upload(s.d_desc, s.stream, false);
         const double t = now_seconds();
         if (rc == TPT_OK) rc = s.exec.enqueue(s.stream);
         if (rc == TPT_OK && hipMemcpyAsync(s.h_stats, s.exec.norms(0), grp.size() * MultiExec::STATS_BYTES,
@@ -242,6 +245,7 @@ bool tpt_server_s::admit_locked() {
         if (rc == TPT_OK && hipEventRecord(s.done, s.stream) != hipSuccess) rc = TPT_ERR_HIP;
         if (rc != TPT_OK) {
             const std::string msg = tpt_last_error();
+            (void)hipStreamSynchronize(s.stream);  // what was enqueued uses the staging and the arena
             for (Request* r : grp) {
                 r->state = rc;
                 r->error = msg;
@@ -273,6 +277,8 @@ bool tpt_server_s::admit_locked() {
 
 void tpt_server_s::loop() {
     (void)hipSetDevice(device);
+    // this thread's sleeps below end on time (the default slack is 50 us)
+    (void)prctl(PR_SET_TIMERSLACK, 1000UL, 0, 0, 0);
     std::unique_lock<std::mutex> lock(mu);
     for (;;) {
         const bool c = complete_locked();
