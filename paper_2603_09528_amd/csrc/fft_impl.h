@@ -15,6 +15,7 @@ using namespace fftc;
 
 constexpr int UT_Q = 3;               // radix-2 stages per pass (points per thread = 2^UT_Q)
 constexpr int UT_NT = 256;            // block size (fewer for N = 2048)
+constexpr int UT_WNT = 512;           // of wide blocks
 
 __host__ __device__ inline int ut_log2(int v) {
     int l = 0;
@@ -23,15 +24,22 @@ __host__ __device__ inline int ut_log2(int v) {
 }
 // threads per line, lines per block and block size for real length n
 __host__ __device__ inline int ut_tpl(int n) { return (n >> 1) > (1 << UT_Q) ? (n >> 1) >> UT_Q : 1; }
-__host__ __device__ inline int ut_lines_per_block(int n) { return n >= 2048 ? 1 : UT_NT / ut_tpl(n); }
-__host__ __device__ inline int ut_threads(int n) { return ut_lines_per_block(n) * ut_tpl(n); }
+__host__ __device__ inline int ut_lines_per_block(int n, bool wide = false) {
+    return wide ? UT_WNT / ut_tpl(n) : n >= 2048 ? 1 : UT_NT / ut_tpl(n);
+}
+__host__ __device__ inline int ut_threads(int n, bool wide = false) { return ut_lines_per_block(n, wide) * ut_tpl(n); }
 // LDS line stride in complex points: M plus one pad slot per sixteen, plus
 // three, so that the lanes of strided (y) lines, which run across lines,
 // fall in different banks
 __host__ __device__ inline int ut_line_stride(int n) { return (n >> 1) + (n >> 5) + 3; }
-__host__ __device__ inline size_t ut_lds_bytes(int n) {
+// Wide blocks of 1024 and more leave the quarter-wave table in memory: two
+// blocks then fit a compute unit (at 512 they fit with it, and the inverse DCT
+// takes 58 instead of 65 us at 256 x 512 x 128).
+__host__ __device__ constexpr bool ut_qmem(int n, bool wide) { return wide && n >= 1024; }
+__host__ __device__ inline size_t ut_lds_bytes(int n, bool wide = false) {
     // line data, then W (N/2 entries) and the quarter-wave table (N/2 + 1)
-    return ((size_t)ut_lines_per_block(n) * ut_line_stride(n) + (size_t)n + 1) * sizeof(double2);
+    const size_t tab = ut_qmem(n, wide) ? (size_t)n / 2 : (size_t)n + 1;
+    return ((size_t)ut_lines_per_block(n, wide) * ut_line_stride(n) + tab) * sizeof(double2);
 }
 
 // Complex FFT of the block's lines in LDS (every thread of the block takes
@@ -68,9 +76,9 @@ __device__ __forceinline__ UtGeom ut_geom(const FftDesc& d, long long blk) {
     g.M = g.N >> 1;
     g.nlog = NL ? NL : ut_log2(g.N);
     g.mlog = g.nlog - 1;
-    g.lpb = ut_lines_per_block(g.N);
+    g.lpb = ut_lines_per_block(g.N, YL == 2);
     g.llog = ut_log2(g.lpb);
-    g.nt = ut_threads(g.N);
+    g.nt = ut_threads(g.N, YL == 2);
     g.ls = ut_line_stride(g.N);
     g.line0 = blk << g.llog;
     g.ly = threadIdx.x & (g.lpb - 1);
@@ -124,13 +132,15 @@ __device__ __forceinline__ int ut_vslot(const UtGeom& g, int l, int j) {
 
 // Copy the twiddle tables of the descriptor into LDS (after the line data):
 // W^k (k < N/2) and, for the cosine and sine transforms, e^{-i pi k/2N}
-// (k <= N/2).  The caller synchronises.
+// (k <= N/2; QMEM: those are read where they lie, the lanes of y lines share a
+// few).  The caller synchronises.
+template <bool QMEM>
 __device__ __forceinline__ void ut_tables(const FftDesc& d, const UtGeom& g, double2* lds, double2*& W,
                                           double2*& Q) {
     W = lds + (size_t)g.lpb * g.ls;
     Q = W + g.M;
     for (int k = threadIdx.x; k < g.M; k += g.nt) W[k] = d.twiddle[k];
-    if (d.kind != UT_FOURIER)
+    if (d.kind != UT_FOURIER && !QMEM)
         for (int k = threadIdx.x; k <= g.M; k += g.nt) Q[k] = d.qtw[k];
 }
 
@@ -191,7 +201,7 @@ template <int NL, int YL, typename TI, typename TO>
 __device__ __forceinline__ void ut_forward_body(const FftDesc& d, long long blk, double2* lds, double* chk) {
     const UtGeom g = ut_geom<NL, YL>(d, blk);
     double2 *W, *Q;
-    ut_tables(d, g, lds, W, Q);
+    ut_tables<ut_qmem(1 << NL, YL == 2)>(d, g, lds, W, Q);
     const int N = g.N, M = g.M, kind = d.kind;
     const TI* in = (const TI*)d.in;
     TO* out = (TO*)d.out;
@@ -385,7 +395,18 @@ __device__ __forceinline__ void ut_forward_body(const FftDesc& d, long long blk,
         return;
     }
     // item m = 0 also writes the output of V_M
-    for (int idx = threadIdx.x; idx < (g.lpb << g.mlog); idx += g.nt) {
+    constexpr bool QMEM = ut_qmem(1 << NL, YL == 2);
+    constexpr int NQ = YL == 2 ? 1 << UT_Q : 1;  // (a thread's items in a wide block)
+    double2 qy[NQ];
+    if constexpr (QMEM) {
+        if (kind != UT_FOURIER) {
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) qy[u] = d.qtw[((int)threadIdx.x + u * g.nt) >> g.llog];
+        }
+    }
+#pragma unroll NQ
+    for (int u = 0; u < (g.lpb << g.mlog) / g.nt; ++u) {
+        const int idx = (int)threadIdx.x + u * g.nt;
         int l, m;
         ut_item<YL>(d, g, g.mlog, idx, l, m);
         if (!ut_valid<YL>(d, g, l)) continue;
@@ -416,7 +437,10 @@ __device__ __forceinline__ void ut_forward_body(const FftDesc& d, long long blk,
                 const double2 zm = a[pad16(m)], zc = conj2(a[pad16(M - m)]);
                 const double2 e = cscale(cadd(zm, zc), 0.5);
                 const double2 t = cmul(W[m], cscale(csub(zm, zc), 0.5));
-                const double2 r = cmul(Q[m], make_double2(e.x + t.y, e.y - t.x));  // e^{-i pi m/2N} V_m
+                double2 q;
+                if constexpr (QMEM) q = qy[u];
+                else q = Q[m];
+                const double2 r = cmul(q, make_double2(e.x + t.y, e.y - t.x));  // e^{-i pi m/2N} V_m
                 out[ut_off<YL>(d, g, l, rev ? N - 1 - m : m)] = (TO)(cb * r.x);
                 out[ut_off<YL>(d, g, l, rev ? m - 1 : N - m)] = (TO)(-cb * r.y);
             }
@@ -447,7 +471,7 @@ template <int NL, int YL, typename TI, typename TO, int EPI>
 __device__ __forceinline__ void ut_inverse(const FftDesc& d, long long blk, double2* lds, double* red) {
     const UtGeom g = ut_geom<NL, YL>(d, blk);
     double2 *W, *Q;
-    ut_tables(d, g, lds, W, Q);
+    ut_tables<ut_qmem(1 << NL, YL == 2)>(d, g, lds, W, Q);
     __syncthreads();
     const int N = g.N, M = g.M, kind = d.kind;
     const TI* in = (const TI*)d.in;
@@ -564,7 +588,7 @@ __device__ __forceinline__ void ut_inverse(const FftDesc& d, long long blk, doub
                 // V_m = e^{i pi m/2N} (X_m - i X_{N-m})
                 const double ca = s * sqrt(1.0 / N), cb = s * sqrt(2.0 / N);
                 F = m == 0 ? make_double2(2.0 * ca * p0[u], sqrt(2.0) * cb * p1[u])
-                           : cmul(conj2(Q[m]), make_double2(cb * p0[u], -cb * p1[u]));
+                           : cmul(conj2(ut_qmem(1 << NL, YL == 2) ? d.qtw[m] : Q[m]), make_double2(cb * p0[u], -cb * p1[u]));
             }
             lds[(size_t)l * g.ls + pad16(m)] = F;
         }
@@ -639,13 +663,13 @@ __device__ __forceinline__ void ut_block(const FftDesc& d, long long blk) {
 // Consecutive blocks of strided lines share cache lines: y launches number
 // their blocks per XCD (xcd_block).
 template <int NL, int YL, typename TI, typename TO, int EPI, bool INV>
-__global__ __launch_bounds__(UT_NT) void ut_kernel(FftDesc d, long long nblocks) {
+__global__ __launch_bounds__(YL == 2 ? UT_WNT : UT_NT) void ut_kernel(FftDesc d, long long nblocks) {
     const long long b = ut_y<YL>(d) ? xcd_block(blockIdx.x, nblocks) : (long long)blockIdx.x;
     ut_block<NL, YL, TI, TO, EPI, INV>(d, b);
 }
 
 template <int NL, int YL, typename TI, typename TO, int EPI, bool INV>
-__global__ __launch_bounds__(UT_NT) void ut_multi_kernel(const FftDesc* __restrict__ work, int nwork,
+__global__ __launch_bounds__(YL == 2 ? UT_WNT : UT_NT) void ut_multi_kernel(const FftDesc* __restrict__ work, int nwork,
                                                          long long total) {
     for (long long blk = blockIdx.x; blk < total; blk += gridDim.x) {
         int lo = 0, hi = nwork - 1;
@@ -662,8 +686,8 @@ __global__ __launch_bounds__(UT_NT) void ut_multi_kernel(const FftDesc* __restri
 
 template <bool MULTI, int NL, int YL, typename TI, typename TO, int EPI, bool INV>
 hipError_t launch_ut_n(const FftDesc& d, const FftDesc* d_work, int nwork, long long blocks, hipStream_t s) {
-    const size_t sm = ut_lds_bytes(d.n);
-    const dim3 nt(ut_threads(d.n));
+    const size_t sm = ut_lds_bytes(d.n, YL == 2);
+    const dim3 nt(ut_threads(d.n, YL == 2));
     if constexpr (MULTI)
         TPT_KLAUNCH((ut_multi_kernel<NL, YL, TI, TO, EPI, INV>),
                     dim3((unsigned)(blocks < 4 * PERSISTENT_BLOCKS ? blocks : 4 * PERSISTENT_BLOCKS)), nt, sm, s, d_work,
@@ -676,6 +700,14 @@ hipError_t launch_ut_n(const FftDesc& d, const FftDesc* d_work, int nwork, long 
 // Lines of 64 and more have kernels for their length and direction.
 template <bool MULTI, int YL, typename TI, typename TO, int EPI, bool INV>
 hipError_t launch_ut_t(const FftDesc& d, const FftDesc* d_work, int nwork, long long blocks, hipStream_t s) {
+    if constexpr (YL == 2) {
+        switch (d.n) {
+            case 512: return launch_ut_n<MULTI, 9, YL, TI, TO, EPI, INV>(d, d_work, nwork, blocks, s);
+            case 1024: return launch_ut_n<MULTI, 10, YL, TI, TO, EPI, INV>(d, d_work, nwork, blocks, s);
+            case 2048: return launch_ut_n<MULTI, 11, YL, TI, TO, EPI, INV>(d, d_work, nwork, blocks, s);
+            default: return hipErrorInvalidValue;
+        }
+    } else
     switch (d.n) {
         case 64: return launch_ut_n<MULTI, 6, YL, TI, TO, EPI, INV>(d, d_work, nwork, blocks, s);
         case 128: return launch_ut_n<MULTI, 7, YL, TI, TO, EPI, INV>(d, d_work, nwork, blocks, s);
@@ -696,11 +728,20 @@ hipError_t launch_ut(const FftDesc& rep, const FftDesc* d_work, int nwork, long 
     if (blocks > 0x7fffffffLL || !fft_supported(rep.n)) return hipErrorInvalidValue;
     if (rep.kind < UT_FOURIER || rep.kind > UT_DST) return hipErrorInvalidValue;
     if (rep.ylines && (rep.inner <= 0 || rep.s_elem <= 0)) return hipErrorInvalidValue;
+    if (rep.wide && !rep.ylines) return hipErrorInvalidValue;
     const bool i64 = rep.tin == DT_F64, o64 = rep.tout == DT_F64;
 #define TPT_UT(YL, TI, TO, EPI, INV) return launch_ut_t<MULTI, YL, TI, TO, EPI, INV>(rep, d_work, nwork, blocks, s)
     if (rep.ylines) {
         // y passes lie between the x passes and the lines: one type in and out
         if (i64 != o64 || rep.epi != EPI_STORE) return hipErrorInvalidValue;
+        if (rep.wide) {
+            if (rep.inverse) {
+                if (i64) TPT_UT(2, double, double, EPI_STORE, true);
+                TPT_UT(2, float, float, EPI_STORE, true);
+            }
+            if (i64) TPT_UT(2, double, double, EPI_STORE, false);
+            TPT_UT(2, float, float, EPI_STORE, false);
+        }
         if (rep.inverse) {
             if (i64) TPT_UT(1, double, double, EPI_STORE, true);
             TPT_UT(1, float, float, EPI_STORE, true);

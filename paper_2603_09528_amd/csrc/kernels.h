@@ -172,6 +172,7 @@ struct FftDesc {
     int kind;               // XformKind
     int inverse;
     int ylines;             // 0: line l starts at l * n; 1: strided as above
+    int wide;               // fft_wide: blocks of more lines
     long long lines;
     long long inner;        // ylines: lines per slab (Nx)
     long long s_elem;       // ylines: element stride (Nx)
@@ -197,7 +198,9 @@ struct FftDesc {
 };
 bool fft_supported(int n);
 long long fft_blocks(const FftDesc& d);
-int fft_lines_per_block(int n);
+int fft_lines_per_block(int n);    // x lines
+// y lines in 512-thread blocks
+int fft_wide(const FftDesc& d);
 hipError_t launch_fft(const FftDesc& d, long long blocks, hipStream_t s);
 // rep: a representative descriptor; every descriptor of the list has its types,
 // direction, epilogue and line length

@@ -207,15 +207,18 @@ int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const s
 }
 
 int MultiExec::add_fft_stage(const std::vector<FftDesc>& fs, const std::vector<char>& use) {
-    // one persistent launch per line length (block shape and LDS depend on it)
-    std::vector<int> lens;
-    for (size_t i = 0; i < fs.size(); ++i)
-        if (use[i] && std::find(lens.begin(), lens.end(), fs[i].n) == lens.end()) lens.push_back(fs[i].n);
-    for (int n : lens) {
+    // one persistent launch per line length and lines per block (block shape
+    // and LDS depend on them)
+    std::vector<std::pair<int, int>> shapes;
+    for (size_t i = 0; i < fs.size(); ++i) {
+        const std::pair<int, int> sh(fs[i].n, fs[i].wide);
+        if (use[i] && std::find(shapes.begin(), shapes.end(), sh) == shapes.end()) shapes.push_back(sh);
+    }
+    for (const auto& sh : shapes) {
         std::vector<FftDesc> grp;
         long long total = 0;
         for (size_t i = 0; i < fs.size(); ++i) {
-            if (!use[i] || fs[i].n != n) continue;
+            if (!use[i] || fs[i].n != sh.first || fs[i].wide != sh.second) continue;
             FftDesc f = fs[i];
             f.block_begin = total;
             total += fft_blocks(f);

@@ -254,6 +254,7 @@ FftDesc stage_fft(const tpt_plan_s* p, int stage, const void* in, int tin, void*
         f.inner = nx;
         f.s_elem = nx;
         f.s_outer = (long long)nx * ny;
+        f.wide = fft_wide(f);
     }
     f.in = in;
     f.out = out;
