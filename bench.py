@@ -829,11 +829,14 @@ def main():
     per_launch_ms = kms / launches
     nalpha = n
     if kname.startswith("gemm") or kname.startswith("xgemm"):
-        # GEMM flops of the y (or x) contraction; a fused kernel's x transform
-        # (about 2.5 log2(Nx) + 6 flops per unknown) runs on the vector ALUs
+        # GEMM flops of the y (or x) contraction: two products of half the size,
+        # N flop per unknown (both directions of the workload are mirror
+        # images of themselves), or the whole basis, 2 N, in the fused kernel,
+        # whose x transform (about 2.5 log2(Nx) + 6 flops per unknown) runs on
+        # the vector ALUs
         dt = kname.rsplit("_", 1)[1]
         mult = 3 if dt == "bf16x3" else 1
-        flops = 2.0 * nalpha * dof * mult
+        flops = (2.0 if kname.startswith("xgemm") else 1.0) * nalpha * dof * mult
         peak = PEAK_TFLOPS["bf16" if dt == "bf16x3" else dt]
         elem = 8 if dt == "f64" else 4
         ai = flops / (2 * elem * dof)

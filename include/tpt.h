@@ -384,7 +384,8 @@ int tpt_server_destroy(tpt_server server);
  * pin_line >= 0 sets the last unknown of that line to zero and drops its
  * last equation (§3 gauge).  f may equal x.
  * variant: -1 automatic (what plans use; partitioned from 16 planes on, plain
- * and cyclic, in further configurations between those numbered below); 0 sequential (one lane per line); 1..17 partitioned (each line cut into
+ * and cyclic, in further configurations between those numbered below);
+ * 0 sequential (one lane per line); 1..17 partitioned (each line cut into
  * P segments of L planes solved in parallel and joined by a P-row interface
  * system, LB lines per block), (LB, P, L) = (64,4,8) (64,8,8) (32,8,8)
  * (64,8,16) (32,8,16) (16,8,16) (64,16,16) (32,16,16) (16,16,16) (64,8,32)
