@@ -221,7 +221,8 @@ template <typename TM, typename TI, typename TO, int EPI, bool Y, bool INV, bool
           int WP, int WD>
 __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, int nwork,
                                            const unsigned* __restrict__ coarse, unsigned total, TM* smem,
-                                           double* red) {
+                                           double* red,
+                                           unsigned block = blockIdx.x, unsigned blocks = gridDim.x) {
     typedef FoldLds<TM, Y, CORR, PH, DN> S;
     static_assert(!CORR || std::is_same<TM, double>::value, "remainders are for FP64");
     typedef FoldCfg<PH, DN, WP, WD> C;
@@ -323,8 +324,9 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             const int o = Y ? (k % 4) * S::PD + line * NK + k / 4 : line * S::PD + (k % 4) * NK + k / 4;
             TM a, b;
             if constexpr (CORR && INV) {
-                a = rr[q].x * r0[q] - rr[q].y * r1[q];
-                b = rr[q].y * r0[q] + rr[q].x * r1[q];
+                // (written as multiply-adds: the same bits in every tile shape)
+                a = __builtin_fma(rr[q].x, (double)r0[q], -(rr[q].y * r1[q]));
+                b = __builtin_fma(rr[q].x, (double)r1[q], rr[q].y * r0[q]);
             } else {
                 a = INV ? (TM)r0[q] : (TM)(r0[q] + r1[q]);
                 b = INV ? (TM)r1[q] : (TM)(r0[q] - r1[q]);
@@ -352,8 +354,8 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         }
     };
 
-    const unsigned grid = gridDim.x;
-    unsigned v = blockIdx.x;
+    const unsigned grid = blocks;
+    unsigned v = block;
     if (v >= total) return;
     // (neighbouring tiles on one XCD)
     auto find = [&](unsigned b) {
@@ -498,8 +500,8 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                         for (int r = 0; r < 4; ++r) {
                             const double2 cs = rot[i * 16 + (Y ? MM::row(lg, r) : lr)];
                             const double e = acc[0][i][j][r], o = acc[1][i][j][r];
-                            acc[0][i][j][r] = cs.x * e + cs.y * o;
-                            acc[1][i][j][r] = cs.x * o - cs.y * e;
+                            acc[0][i][j][r] = __builtin_fma(cs.x, e, cs.y * o);
+                            acc[1][i][j][r] = __builtin_fma(cs.x, o, -(cs.y * e));
                         }
                     }
                 }

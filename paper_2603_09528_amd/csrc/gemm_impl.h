@@ -514,7 +514,8 @@ __device__ __forceinline__ void wl_find(const GemmDesc* __restrict__ work, int n
 
 template <typename TM, typename TA, typename TB, typename TC, int EPI, bool BNK, int BM, int BN>
 __device__ __forceinline__ void gemm_worklist_f(const GemmDesc* __restrict__ work, int nwork, long long total,
-                                                TM* smem, double* red) {
+                                                TM* smem, double* red, unsigned block = blockIdx.x,
+                                                unsigned blocks = gridDim.x) {
     typedef WlCfg<BM, BN> W;
     constexpr int BK = W::BK, NT = W::NT, LA = W::LA, LB = W::LB, MI = W::MI, NI = W::NI;
     typedef SmemF<TM, BM, BN, BNK, BK, 2> S;
@@ -590,8 +591,8 @@ __device__ __forceinline__ void gemm_worklist_f(const GemmDesc* __restrict__ wor
         }
     };
 
-    const long long grid = gridDim.x;
-    long long v = blockIdx.x;
+    const long long grid = blocks;
+    long long v = block;
     if (v >= total) return;
     WlTile cur, nxt;
     __amdgpu_buffer_rsrc_t rA, rB, nA, nB;

@@ -157,6 +157,10 @@ std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long tota
 hipError_t launch_fold(FoldDesc g, hipStream_t s);
 hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
+// tiles (16 x 64, remainders applied) of the list and the FP64 work-list tiles of
+// the same stage
+hipError_t launch_fold_gemm(const FoldDesc& rep, const FoldList& list, long long ftiles, const GemmDesc* gemm, int ngemm,
+                            long long gtiles, hipStream_t s);
 hipError_t launch_fold_bf16(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f32(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 

@@ -156,25 +156,34 @@ int MultiExec::add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& 
 }
 
 // Tiles (of 32 x 128) up to which one kind of half-size products joins the
-// launch of the other: 16 uneven problems of 24 to 192 cells a direction 1100
+// launch of the other: 16 uneven problems of 48 to 192 cells a direction 1100
 // us a batch apart, 1095 up to 512 tiles, 1074 up to 2048; ten requests of 64
-// to 224, 2240, 2230, 2216, and 2370 always together.
+// to 256, 2240, 2230, 2216, and 2370 always together.
 constexpr long long FOLD_MERGE = 2048;
+// Tiles of either kind up to which a stage's half-size products (16 x 64) share
+// a launch with its work-list GEMM: a batch of 12 problems of 29 to 100 cells a
+// direction 261 us apart and 241 joined, of 18 of 31 to 98, 333 and 315; larger
+// ones lose by the small tile (ten requests of 64 to 256, always joined: 2345
+// against 2190).
+constexpr long long FOLD_JOIN = 3072;
 
 int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const std::vector<char>& use,
-                              std::vector<long long>* nb) {
+                              std::vector<long long>* nb, bool with_gemm) {
     // one persistent launch for the problems with remainders and one for the
     // others; a few tiles join the others' launch instead (their remainders are
     // zero: 13 % more time a tile at 256^3, against a launch of its own with
     // most of the device idle).  Every tile shape gives the same bits, and so do
     // zero remainders, so batch and single results agree.
-    long long tiles[2] = {0, 0};
+    long long tiles[2] = {0, 0}, small = 0;
     for (size_t i = 0; i < gs.size(); ++i)
         if (use[i]) {
             FoldDesc g = gs[i];
             tiles[g.corr] += fold_tiles(g, FOLD_32x128);
+            small += fold_tiles(g, FOLD_16x64);
         }
-    const bool merge = tiles[0] > 0 && tiles[1] > 0 && std::min(tiles[0], tiles[1]) <= FOLD_MERGE;
+    // with_gemm: the stage's only other launch is a work-list GEMM
+    const bool join = with_gemm && prec == GP_F64 && small > 0 && small <= FOLD_JOIN && seq_.back().total <= FOLD_JOIN;
+    const bool merge = join || tiles[0] > 0 && tiles[1] > 0 && std::min(tiles[0], tiles[1]) <= FOLD_MERGE;
     for (int corr = merge ? 1 : 0; corr < 2; ++corr) {
         std::vector<FoldDesc> grp;
         std::vector<size_t> idx;
@@ -185,7 +194,7 @@ int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const s
             idx.push_back(i);
         }
         if (grp.empty()) continue;
-        const int shape = fold_shape(grp.data(), (int)grp.size());
+        const int shape = join ? (int)FOLD_16x64 : fold_shape(grp.data(), (int)grp.size());
         long long total = 0;
         for (size_t k = 0; k < grp.size(); ++k) {
             const long long t = fold_tiles(grp[k], shape);
@@ -201,6 +210,13 @@ int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const s
         L.off2 = append(blob_, fold_coarse(grp, total));
         L.nwork = (int)grp.size();
         L.total = total;
+        if (join) {
+            L.kind = 11;
+            L.off3 = seq_.back().off;
+            L.nwork3 = seq_.back().nwork;
+            L.total3 = seq_.back().total;
+            seq_.pop_back();
+        }
         seq_.push_back(L);
     }
     return TPT_OK;
@@ -281,8 +297,9 @@ int MultiExec::build(const double* const* rhs, double* const* out, void* ws) {
                 g[i] = stage_gemm(plans_[i], st, prec_, in[i], tin, outp[i], tout, epi, part, 1);
             }
         }
+        const size_t before = seq_.size();
         add_gemm_stage(st, prec_, g, form_mask(st, BF_DENSE), nb);
-        add_fold_stage(prec_, h, form_mask(st, BF_FOLD), nb);
+        add_fold_stage(prec_, h, form_mask(st, BF_FOLD), nb, seq_.size() == before + 1 && seq_.back().kind == 8);
         add_fft_stage(f, form_mask(st, BF_FAST));
     };
     std::vector<void*> w1(n), w2(n), outv(n);
@@ -463,6 +480,13 @@ int MultiExec::enqueue(hipStream_t s) const {
                 const FoldDesc& rep = *(const FoldDesc*)(blob_.data() + L.off);
                 const FoldList list{(const FoldDesc*)(d_desc_ + L.off), L.nwork, (const unsigned*)(d_desc_ + L.off2)};
                 e = launch_fold_multi(rep, list, L.total, L.variant, s);
+                break;
+            }
+            case 11: {
+                TimedScope ts("multi_gemm", s);
+                const FoldDesc& rep = *(const FoldDesc*)(blob_.data() + L.off);
+                const FoldList list{(const FoldDesc*)(d_desc_ + L.off), L.nwork, (const unsigned*)(d_desc_ + L.off2)};
+                e = launch_fold_gemm(rep, list, L.total, (const GemmDesc*)(d_desc_ + L.off3), L.nwork3, L.total3, s);
                 break;
             }
             case 8: {

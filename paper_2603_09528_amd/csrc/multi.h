@@ -41,7 +41,8 @@ class MultiExec {
                       // 6 right-hand-side check, 7 folding of fused-check partials,
                       // 8 work-list GEMM (persistent, all problems of the stage),
                       // 9 one GEMM problem on its own (single-problem kernel),
-                      // 10 half-size products of mirror directions (variant: tile shape)
+                      // 10 half-size products of mirror directions (variant: tile shape),
+                      // 11 those and the work-list GEMM of a stage of small problems
         // sequential Thomas: variant holds the largest nz; partitioned: the
         // configuration, prec the storage type, b_nk set for cyclic lines
         int prec, variant, b_nk;
@@ -49,13 +50,16 @@ class MultiExec {
         size_t off2;  // half-size products: byte offset of the problems of the tiles (FoldList)
         int nwork;
         long long total;
+        size_t off3;  // kind 11: the work list
+        int nwork3;
+        long long total3;
     };
     // nb (if given): per problem of the stage, the blocks / tiles its GEMM
     // launch runs (the norm partials an accumulating stage writes)
     int add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& g, const std::vector<char>& use,
                        std::vector<long long>* nb = nullptr);
     int add_fold_stage(int prec, const std::vector<FoldDesc>& g, const std::vector<char>& use,
-                       std::vector<long long>* nb);
+                       std::vector<long long>* nb, bool with_gemm);
     int add_fft_stage(const std::vector<FftDesc>& f, const std::vector<char>& use);
     std::vector<tpt_plan_s*> plans_;
     int prec_ = GP_F64;

@@ -439,12 +439,16 @@ static int part_index(int lb, int p, int l) {
 //   lines of 640: 216 against 248 us, 40 000: 145 against 84; 1 M lines of 512:
 //   1.51 against 1.76 ms).  Cyclic lines stay partitioned (262 144 lines of
 //   1024: 1.56 against 2.15 ms).
+// - Few lines take two lengths from 65 to 192 planes, not five: alone 4096 lines
+//   lose less than 1 us by it, and small problems of a batch share a launch
+//   where they share a configuration.
 static int thomas_part_auto(int nz, long long lines, bool f32, bool cyc) {
     if (!cyc) {
         if (nz > 512 && lines >= (f32 ? 98304 : 524288)) return -1;
         if (f32 && nz > 384 && lines >= 524288) return -1;
     }
     const bool many = lines >= 262144, wide = lines >= 98304;
+    if (lines < 16384 && nz > 64 && nz <= 192) return nz <= 128 ? part_index(32, 8, 16) : part_index(32, 16, 12);
     if (nz <= 32) return part_index(64, 4, 8);
     if (nz <= 64) return part_index(32, 8, 8);
     if (nz <= 96) return part_index(32, 8, 12);
