@@ -92,8 +92,9 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("kernels.hip", "thomas_part.hip", "fft.hip", "fft_core.h", "xgemm.hip", "gemm_f64.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_impl.h",
-                  "device_common.h", "kernels.h")
+KERNEL_SOURCES = ("kernels.hip", "thomas_part.hip", "fft.hip", "fft_multi.hip", "fft_impl.h", "fft_core.h", "xgemm.hip",
+                  "gemm_f64.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_impl.h", "mfma_tile.h", "fold_f64.hip",
+                  "fold_f32.hip", "fold_bf16.hip", "fold_impl.h", "device_common.h", "kernels.h")
 
 
 def kernel_hash():
