@@ -29,6 +29,19 @@ long long fold_tiles(FoldDesc& g, int shape) {
     return (long long)g.tiles_p * ((g.lines + dn - 1) / dn);
 }
 
+static int fold_shapes(int prec) { return prec == GP_BF16X3 ? 2 : (int)FOLD_NSHAPE; }
+
+long long fold_max_tiles(int n, long long lines, int prec) {
+    FoldDesc g{};
+    g.n = n;
+    g.h = (n + 1) / 2;
+    g.prec = prec;
+    g.lines = lines;
+    long long most = 0;
+    for (int v = 0; v < fold_shapes(prec); ++v) most = std::max(most, fold_tiles(g, v));
+    return most;
+}
+
 // Relative time of a launch of `tiles` tiles: what the compute unit with most
 // tiles has to do, over the rate the shape reaches when it has enough.  The
 // padding of h to whole tiles and the idle units of a last round are in the
@@ -49,7 +62,7 @@ static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
 int fold_shape(const FoldDesc* g, int count) {
     int best = 0;
     double cost = 0.0;
-    for (int v = 0; v < (g[0].prec == GP_BF16X3 ? 2 : (int)FOLD_NSHAPE); ++v) {
+    for (int v = 0; v < fold_shapes(g[0].prec); ++v) {
         long long tiles = 0;
         for (int i = 0; i < count; ++i) {
             FoldDesc t = g[i];

@@ -127,7 +127,7 @@ struct FoldDesc {
     long long lines;        // x: Ny Nz nrhs; y: Nx Nz nrhs
     int tin, tout;          // DType of in / out
     int epi;                // EPI_STORE, or EPI_ACCUM_F64 (inverse x lines, FP64 out)
-    double* partials;       // EPI_ACCUM_F64: 2 doubles per tile
+    double* partials;       // EPI_ACCUM_F64: 2 doubles per tile (fold_max_tiles at most)
     int tiles_p;            // tiles along the modes (fold_tiles sets it)
     long long block_begin;  // multi-problem
 };
@@ -145,6 +145,8 @@ inline int fold_cols(int prec) { return prec == GP_BF16X3 ? 32 : FOLD_COLS; }
 // every shape gives the same bits).
 int fold_shape(const FoldDesc* g, int count);
 long long fold_tiles(FoldDesc& g, int shape);       // sets tiles_p; the tile count
+// The most tiles that any shape makes of x lines of n unknowns (no remainders).
+long long fold_max_tiles(int n, long long lines, int prec);
 // Blocks of a launch of `total` tiles: at most what the GPU holds at once (two
 // blocks of eight waves, three of four, five of the small tile per CU).
 long long fold_grid(const FoldDesc& g, int shape, long long total);

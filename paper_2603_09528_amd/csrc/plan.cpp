@@ -312,11 +312,15 @@ int plan_gemm_prec(const tpt_plan_s* p) {
 // FP32 residual; the tail holds partial sums.
 static size_t partial_slots(const tpt_plan_s* p) {
     const long long dof = p->dof * p->desc.nrhs;
-    // enough for the residual blocks of all rhs and for the x-inverse GEMM
-    // blocks of the smallest tile (32 x 64)
+    // enough for the residual blocks of all rhs, for the x-inverse GEMM blocks
+    // of its smallest tile (32 x 64) and for the tiles of the x-inverse
+    // half-size products (those have fewer lines to a tile: few long x lines
+    // make more of them)
     long long res = 0;
     for (int r = 0; r < p->desc.nrhs; ++r) res += (p->dof + 255) / 256;
     long long xi = ((long long)p->N[1] * p->N[2] * p->desc.nrhs + 31) / 32 * ((p->N[0] + 63) / 64);
+    if (p->desc.precision != TPT_FP64)
+        xi = std::max(xi, fold_max_tiles(p->N[0], (long long)p->N[1] * p->N[2], plan_gemm_prec(p)));
     // the x-inverse fast transform: at most one block per x line
     const long long fx = (long long)p->N[1] * p->N[2] * p->desc.nrhs;
     // the right-hand-side check: 4 doubles (two slots) per block
