@@ -23,11 +23,13 @@
 // undoes the mixing of pairs whose eigenvalues agree to that), and CORR adds
 // what is left:
 //   E += X0 (f_k - f_{N-1-k}),  O += X1 (f_k + f_{N-1-k}),  then the rotation,
-// and the same, backwards, in the inverse.  X is 1e-13 of P, so eight bits of
-// it and of the data are enough: BF16 products in FP32 accumulators, an eighth
-// of the FP64 products' time.  Together P, X and the rotation are the full
-// dense basis to the rounding of a double; without X, errors of 1e-13 would be
-// left where the dense product has 1e-15.
+// and the same, backwards, in the inverse.  X is at most 5e-12 of P, so two
+// BF16 terms of it and of the data (16 bits each) leave 2^-55 of a vector:
+// all four products of the terms of eight columns are one K = 32 BF16 product
+// in FP32 accumulators, an eighth of the FP64 products' time.  Together P, X
+// and the rotation are the dense basis to the rounding of a double (one term
+// would leave 2e-16 .. 7e-15 on tanh grids); without X, errors of 1e-13 would
+// be left where the dense product has 1e-15.
 //
 // P0, P1 are padded with zero rows and columns (rows to 64, row length to
 // 16), so basis loads need no bounds and the K loop no tail, and stored by
@@ -52,8 +54,9 @@ namespace tpt {
 // lane reads are its operands of all the step's MFMAs (column 4 m + l / 16 of
 // the m-th): P as [parity][PH][BK], the data as [parity][4][DN][BK / 4] (y
 // lines) or [parity][DN][BK] (x lines), rows padded by 16 bytes.
-// CORR keeps 16 columns (two K steps) of the remainders, [parity][PH][16], and
-// of the data's BF16 copies, [parity][DN][16], rows padded to 40 bytes.
+// CORR keeps the remainders, [parity][PH][16], and the data's BF16 copies,
+// [parity][DN][16], a row the high terms of the step's columns and then the low
+// ones, rows padded to 40 bytes.
 template <typename TM, bool Y, bool CORR, int PH, int DN> struct FoldLds {
     static constexpr int BK = 64 / (int)sizeof(TM), NK = BK / 4;
     static constexpr int PP = BK + NK;
@@ -103,13 +106,16 @@ __device__ __forceinline__ FoldTile fold_find(const FoldDesc* __restrict__ work,
     return t;
 }
 
-// BF16 pair of two values (to nearest, magnitudes past the FP32 range held at
-// its end: a product with a zero remainder stays zero)
-__device__ __forceinline__ uint32_t fold_bf16x2(float a, float b) {
-    const tpt_f32x2 v = {__builtin_amdgcn_fmed3f(a, -3e38f, 3e38f), __builtin_amdgcn_fmed3f(b, -3e38f, 3e38f)};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, tpt_bf16x2));
+// Two BF16 terms of two values (magnitudes past the FP32 range held at its end:
+// a product with a zero remainder stays zero)
+__device__ __forceinline__ void fold_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+    split_bf16x2(__builtin_amdgcn_fmed3f(a, -3e38f, 3e38f), __builtin_amdgcn_fmed3f(b, -3e38f, 3e38f), hi, lo);
 }
-typedef short s16x4 __attribute__((ext_vector_type(4)));
+// Eight BF16 values from an 8-byte aligned address
+__device__ __forceinline__ bf16x8 fold_frag(const uint16_t* p) {
+    const u32x2_t a = *(const u32x2_t*)p, b = *(const u32x2_t*)(p + 4);
+    return __builtin_bit_cast(bf16x8, (u32x4_t){a[0], a[1], b[0], b[1]});
+}
 
 // The FP32 MFMA leaves rows 4 g + r of a 16 x 16 result in lane group g (of
 // 16 lanes), register r; the FP64 one rows g + 4 r.  Transposing (g, r) makes
@@ -224,7 +230,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                                            double* red,
                                            unsigned block = blockIdx.x, unsigned blocks = gridDim.x) {
     typedef FoldLds<TM, Y, CORR, PH, DN> S;
-    static_assert(!CORR || std::is_same<TM, double>::value, "remainders are for FP64");
+    static_assert(!CORR || std::is_same<TM, double>::value, "remainders are for FP64");  // (BK = 8)
     typedef FoldCfg<PH, DN, WP, WD> C;
     typedef Mfma<TM> MM;
     constexpr int BK = S::BK, NT = C::NT, MP = C::MP, MD = C::MD;
@@ -261,8 +267,8 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         const FoldDesc& g = desc(t);
         rP = buf_rsrc(g.P);
         o.p = (unsigned)((((prow / PH) * g.hp + prow % PH) * BK + pcol * NK) * em);
-        // remainders of a pair of K steps: a quarter row of 16 per thread
-        if constexpr (CORR) o.x = (unsigned)((((prow / PH) * g.hp + prow % PH) * 16 + pcol * 4) * 2);
+        // remainders: a quarter row of both terms per thread
+        if constexpr (CORR) o.x = (unsigned)((((prow / PH) * g.hp + prow % PH) * 2 * BK + pcol * 4) * 2);
         const int km = BK - LK - dk;  // the mirrors of rows dk .. dk + LK - 1, ascending
         if constexpr (Y) {
             // column c = slab * inner + i; offsets from the tile's first slab
@@ -304,13 +310,11 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             if constexpr (CORR && INV) rr[q] = g.rot[k];
         }
         if constexpr (CORR) {
-            // (also in the second step of a pair: no branch around a load)
             const __amdgpu_buffer_rsrc_t rX = buf_rsrc(g.X);
-            rx = __builtin_amdgcn_raw_buffer_load_b64(rX, (int)o.x, (int)(((k0 & ~15) * 2 * g.hp + t.p0 * 16) * 2), 0);
+            rx = __builtin_amdgcn_raw_buffer_load_b64(rX, (int)o.x, (int)((k0 * 2 * g.hp + t.p0 * BK) * 4), 0);
         }
     };
-    // kb: position of the K step in its pair (CORR: which half of the copies)
-    auto sstore = [&](int buf, int kb, int bbuf) {
+    auto sstore = [&](int buf) {
         TM* P = smem + buf * S::BUF + prow * S::PP + pcol * NK;
         TM* D = smem + buf * S::BUF + 2 * S::P_HALF;
         if (NT <= 8 * PH || tid < 8 * PH) {
@@ -337,18 +341,25 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             c1[q] = (float)b;
         }
         if constexpr (CORR) {
-            uint16_t* B = (uint16_t*)(smem + 2 * S::BUF) + bbuf * S::B_BUF + dline * S::PB + kb * BK + dk;
-            // (the second step of a pair writes the same remainders again)
-            if (NT == 8 * PH || tid < 8 * PH) *(u32x2_t*)(B - (dline * S::PB + kb * BK + dk) + 2 * S::B_HALF + prow * S::PB + pcol * 4) = rx;
+            uint16_t* C = (uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
+            uint16_t* B = C + dline * S::PB + dk;
+            if (NT == 8 * PH || tid < 8 * PH) *(u32x2_t*)(C + 2 * S::B_HALF + prow * S::PB + pcol * 4) = rx;
+            uint32_t hi, lo;
             if constexpr (LD == 1) {
-                const uint32_t w = fold_bf16x2(c0[0], c1[0]);
-                B[0] = (uint16_t)w;
-                B[S::B_HALF] = (uint16_t)(w >> 16);
+                fold_split2(c0[0], c1[0], hi, lo);
+                B[0] = (uint16_t)hi;
+                B[BK] = (uint16_t)lo;
+                B[S::B_HALF] = (uint16_t)(hi >> 16);
+                B[S::B_HALF + BK] = (uint16_t)(lo >> 16);
             } else {
 #pragma unroll
                 for (int q = 0; q < LD; q += 2) {
-                    *(uint32_t*)(B + q) = fold_bf16x2(c0[q], c0[q + 1]);
-                    *(uint32_t*)(B + S::B_HALF + q) = fold_bf16x2(c1[q], c1[q + 1]);
+                    fold_split2(c0[q], c0[q + 1], hi, lo);
+                    *(uint32_t*)(B + q) = hi;
+                    *(uint32_t*)(B + BK + q) = lo;
+                    fold_split2(c1[q], c1[q + 1], hi, lo);
+                    *(uint32_t*)(B + S::B_HALF + q) = hi;
+                    *(uint32_t*)(B + S::B_HALF + BK + q) = lo;
                 }
             }
         }
@@ -371,7 +382,6 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
     __amdgpu_buffer_rsrc_t rP, rD;
     Offs off;
     setup(lt, rP, rD, off);
-    int held = 0;                        // K step (of its tile) in the registers
     auto load_next = [&]() {
         if (lk == lnk) {
             lk = 0;
@@ -385,15 +395,11 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                 ++ahead;
             }  // else past the last tile: its K steps again, never used
         }
-        held = lk;
         gload(lt, rP, rD, off, lk * BK);
         ++lk;
     };
-    // BF16 copies: the pair of K steps being stored and the one being read
-    [[maybe_unused]] int sb = 1, rb = 0;
     auto stage_held = [&](int buf) {
-        if (!(held & 1)) sb ^= 1;
-        sstore(buf, held & 1, sb);
+        sstore(buf);
         load_next();
     };
     load_next();
@@ -421,7 +427,6 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                     for (int j = 0; j < MD; ++j) cacc[q][i][j] = (f4){0.f, 0.f, 0.f, 0.f};
         }
         for (int kt = 0; kt < nk; ++kt) {
-            const bool pair = CORR && ((kt & 1) || kt + 1 == nk);  // the pair of K steps is complete
             const TM* P = smem + buf * S::BUF + (wp * WP + lr) * S::PP + lg * NK;
             const TM* D = smem + buf * S::BUF + 2 * S::P_HALF +
                           (Y ? lg * S::PD + (wd * WD + lr) * NK : (wd * WD + lr) * S::PD + lg * NK);
@@ -449,32 +454,30 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             // the MFMAs, so that the wait for its loads overlaps them, and the
             // loads of the one after it are issued
             stage_held(buf ^ 1);
-            if constexpr (CORR) {
-                if (pair) {
-                    const uint16_t* B = (const uint16_t*)(smem + 2 * S::BUF) + rb * S::B_BUF + (wd * WD + lr) * S::PB + lg * 4;
-                    const uint16_t* X = (const uint16_t*)(smem + 2 * S::BUF) + rb * S::B_BUF + 2 * S::B_HALF +
-                                        (wp * WP + lr) * S::PB + lg * 4;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-#pragma unroll
-                        for (int j = 0; j < MD; ++j) {
-                            uint2 u = *(const uint2*)(B + q * S::B_HALF + j * 16 * S::PB);
-                            if (!(kt & 1) && lg >= 2) u = make_uint2(0u, 0u);  // no second K step
-                            const s16x4 dv = __builtin_bit_cast(s16x4, u);
-#pragma unroll
-                            for (int i = 0; i < MP; ++i) {
-                                const s16x4 xv = *(const s16x4*)(X + (1 - q) * S::X_HALF + i * 16 * S::PB);
-                                cacc[1 - q][i][j] =
-                                    Y ? __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xv, dv, cacc[1 - q][i][j], 0, 0, 0)
-                                      : __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(dv, xv, cacc[1 - q][i][j], 0, 0, 0);
-                            }
-                        }
-                    }
-                    rb ^= 1;
-                }
-            }
 #pragma unroll
             for (int kk = NK / 2; kk < NK; ++kk) multiply(kk);
+            if constexpr (CORR) {
+                // K = 32: the columns by (high, low, high, low) terms of the
+                // remainders and (high, high, low, low) ones of the data
+                const uint16_t* C = (const uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
+                const uint16_t* B = C + (wd * WD + lr) * S::PB + (lg >> 1) * BK;
+                const uint16_t* X = C + 2 * S::B_HALF + (wp * WP + lr) * S::PB + (lg & 1) * BK;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    bf16x8 xv[MP];
+#pragma unroll
+                    for (int i = 0; i < MP; ++i) xv[i] = fold_frag(X + (1 - q) * S::X_HALF + i * 16 * S::PB);
+#pragma unroll
+                    for (int j = 0; j < MD; ++j) {
+                        const bf16x8 dv = fold_frag(B + q * S::B_HALF + j * 16 * S::PB);
+#pragma unroll
+                        for (int i = 0; i < MP; ++i)
+                            cacc[1 - q][i][j] =
+                                Y ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[i], dv, cacc[1 - q][i][j], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv, xv[i], cacc[1 - q][i][j], 0, 0, 0);
+                    }
+                }
+            }
             if (kt + 1 < nk) {
                 __syncthreads();
                 buf ^= 1;
@@ -482,7 +485,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         }
         double se = 0.0, sx = 0.0;
         if constexpr (CORR) {
-            constexpr double xs = 1.0 / FOLD_XSCALE;
+            const double xs = g.xs;
             const double2* rot = g.rot + cur.p0 + wp * WP;
 #pragma unroll
             for (int i = 0; i < MP; ++i) {

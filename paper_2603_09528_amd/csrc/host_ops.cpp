@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <limits>
 #include <numeric>
 
@@ -502,11 +503,43 @@ bool fold_basis(const Op1D& op, const Eig1D& e, int hp, int kp, FoldBasis& f) {
             f.xinv[ka] = (double)(0.5L * (je + jm));
             f.xinv[half + ka] = (double)(0.5L * (ie - im));
         }
-        // the remainders are applied with eight significant bits: at most
-        // 5e-12 of the vector keeps their rounding near that of a double
+        // the kernel's two BF16 terms of remainders and data, 16 bits each, lose
+        // 2^-17 of a remainder at most: of 5e-12 of the vector 2^-54.5, where
+        // rounding the vector itself to doubles takes 2^-53
         if (!(xe <= 2.5e-23L && xo <= 2.5e-23L)) return false;
     }
+    auto scale = [](const std::vector<double>& x) {
+        double m = 0.0;
+        for (double v : x) m = std::max(m, std::fabs(v));
+        int e = 0;
+        std::frexp(m, &e);
+        return std::ldexp(1.0, e);
+    };
+    if (f.rotated) {
+        f.sfwd = scale(f.xfwd);
+        f.sinv = scale(f.xinv);
+    }
     return true;
+}
+
+uint16_t host_bf16(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+
+float host_bf16_to_f(uint16_t h) {
+    uint32_t u = ((uint32_t)h) << 16;
+    float f;
+    std::memcpy(&f, &u, 4);
+    return f;
+}
+
+void fold_split(double x, double s, uint16_t& hi, uint16_t& lo) {
+    hi = host_bf16((float)(x / s));
+    lo = host_bf16((float)(x / s - (double)host_bf16_to_f(hi)));
 }
 
 std::string eig_op1d(const Op1D& op, Eig1D& e) {

@@ -1,6 +1,7 @@
 // Host-side building blocks of a plan: 1-D operators with boundary rows and
 // the eigendecomposition of the symmetrised operator (§2.2.1).
 #pragma once
+#include <cstdint>
 #include <string>
 #include <vector>
 
@@ -57,7 +58,13 @@ struct FoldBasis {
     int hp = 0, kp = 0;
     bool rotated = false;            // rot and xfwd / xinv are not trivial
     std::vector<double> fwd, inv, xfwd, xinv, rot;
+    double sfwd = 1.0, sinv = 1.0;   // powers of two: the largest |xfwd| / sfwd, |xinv| / sinv in [0.5, 1)
 };
+// BF16 of a float (round to nearest even, infinities and NaN kept), and back.
+uint16_t host_bf16(float x);
+float host_bf16_to_f(uint16_t h);
+// The remainders are held as two BF16 terms: x / s = hi + lo.
+void fold_split(double x, double s, uint16_t& hi, uint16_t& lo);
 // Whether the basis splits like this with xfwd, xinv small enough for the
 // kernel's split of them (always for an exact mirror operator).
 bool fold_basis(const Op1D& op, const Eig1D& e, int hp, int kp, FoldBasis& f);

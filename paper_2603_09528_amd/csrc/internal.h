@@ -48,10 +48,12 @@ struct DirBasis {
     float* fs_q = nullptr;
     uint16_t* fb_qinv = nullptr;     // bf16 hi and lo planes
     uint16_t* fb_q = nullptr;
-    // remainders of bases symmetric only up to the rounding of the faces (bf16,
-    // scaled, FP64 plans) and the rotation of each slot; null otherwise
+    // remainders of bases symmetric only up to the rounding of the faces (two
+    // bf16 terms over the powers of two fxs, FP64 plans) and the rotation of
+    // each slot; null otherwise
     uint16_t* fx_qinv = nullptr;
     uint16_t* fx_q = nullptr;
+    double fxs_qinv = 1.0, fxs_q = 1.0;
     double2* f_rot = nullptr;
     int f_corr = 0;                  // fx and f_rot are not trivial
     int hp = 0, kp = 0;

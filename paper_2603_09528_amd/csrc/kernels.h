@@ -110,12 +110,14 @@ hipError_t launch_gemm_bf16(const GemmDesc& g, const GemmDesc* d_work, int nwork
 // columns of each z slab (column c = slab * inner + i).  P holds the padded
 // even and odd bases by K step, in the compute type or as BF16 hi and lo
 // planes; the modes of a line are kept even ones first.  X and rot (FP64): the
-// remainders and rotations of a basis that is symmetric only up to rounding
-// (corr; zero and trivial for an exactly symmetric one).
+// remainders (two BF16 terms of X / xs) and rotations of a basis that is
+// symmetric only up to rounding (corr; zero and trivial for an exactly
+// symmetric one).
 struct FoldDesc {
     const void* P;
     const uint16_t* X;
     const double2* rot;
+    double xs;              // a power of two
     const void* in;
     void* out;
     int n, h;               // line length and (n + 1) / 2
@@ -132,7 +134,6 @@ struct FoldDesc {
     long long block_begin;  // multi-problem
 };
 enum { FOLD_ROWS = 64, FOLD_COLS = 16, FOLD_MIN_N = 16, FOLD_COARSE = 32 };
-constexpr double FOLD_XSCALE = 16777216.0;  // of the remainders (2^24)
 // Tile shapes: slots x lines (with remainders 64 x 64 instead of 64 x 128; split
 // BF16 has 64 x 128 and, in place of 32 x 128, 32 x 64).
 enum FoldShape { FOLD_64x128 = 0, FOLD_32x128 = 1, FOLD_16x64 = 2, FOLD_NSHAPE = 3 };

@@ -18,21 +18,6 @@ int fail(int code, const std::string& msg) {
 }
 const char* last_error_cstr() { return g_last_error.c_str(); }
 
-// ---- bf16 rounding on the host (round to nearest even) ----------------------
-static uint16_t host_bf16(float x) {
-    uint32_t u;
-    std::memcpy(&u, &x, 4);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-static float host_bf16_to_f(uint16_t h) {
-    uint32_t u = ((uint32_t)h) << 16;
-    float f;
-    std::memcpy(&f, &u, 4);
-    return f;
-}
-
 DirBasis::~DirBasis() {
     if (block) {
         int cur = 0;
@@ -132,8 +117,8 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             o_qinv = take(es * nf);
             o_q = take(es * nf);
             if (prec == GP_F64) {
-                o_xqinv = take(2 * nf);
-                o_xq = take(2 * nf);
+                o_xqinv = take(4 * nf);
+                o_xq = take(4 * nf);
                 o_rot = take(8 * fb.rot.size());
             }
         } else {
@@ -169,11 +154,11 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             }
         } else if (form == BF_FOLD) {
             // by K step: [columns / w][parity][row][w], w = 64 bytes of
-            // elements with column k of the step at (k % 4, k / 4), or 16
-            // columns of the remainders in order
-            auto at = [&](size_t e, int w, bool plain = false) {
+            // elements with column k of the step at (k % 4, k / 4); of the
+            // remainders [step of 8][parity][row][high, low terms][8]
+            auto at = [&](size_t e, int w) {
                 const size_t par = e / ((size_t)hp * kp), row = e / kp % hp, c = e % kp, k = c % w;
-                return ((c / w * 2 + par) * hp + row) * w + (plain ? k : k % 4 * (w / 4) + k / 4);
+                return ((c / w * 2 + par) * hp + row) * w + k % 4 * (w / 4) + k / 4;
             };
             double* dqinv = (double*)(host.data() + o_qinv);
             double* dq = (double*)(host.data() + o_q);
@@ -203,8 +188,10 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
                 uint16_t* xi = (uint16_t*)(host.data() + o_xqinv);
                 uint16_t* xq = (uint16_t*)(host.data() + o_xq);
                 for (size_t e = 0; e < nf; ++e) {
-                    xi[at(e, 16, true)] = host_bf16((float)(fb.xfwd[e] * FOLD_XSCALE));
-                    xq[at(e, 16, true)] = host_bf16((float)(fb.xinv[e] * FOLD_XSCALE));
+                    const size_t par = e / ((size_t)hp * kp), row = e / kp % hp, c = e % kp;
+                    const size_t o = ((c / 8 * 2 + par) * hp + row) * 16 + c % 8;
+                    fold_split(fb.xfwd[e], fb.sfwd, xi[o], xi[o + 8]);
+                    fold_split(fb.xinv[e], fb.sinv, xq[o], xq[o + 8]);
                 }
                 std::memcpy(host.data() + o_rot, fb.rot.data(), 8 * fb.rot.size());
             }
@@ -271,6 +258,8 @@ std::shared_ptr<DirBasis> basis_cache_get(const Op1D& op, int ncells, const doub
             }
             if (prec == GP_F64) {
                 b->f_corr = fb.rotated ? 1 : 0;
+                b->fxs_qinv = fb.sfwd;
+                b->fxs_q = fb.sinv;
                 b->fx_qinv = (uint16_t*)(d + o_xqinv);
                 b->fx_q = (uint16_t*)(d + o_xq);
                 b->f_rot = (double2*)(d + o_rot);

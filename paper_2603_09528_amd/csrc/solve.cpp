@@ -214,6 +214,7 @@ FoldDesc stage_fold(const tpt_plan_s* p, int stage, const void* in, int tin, voi
     } else if (g.prec == GP_F64) {
         g.P = fwd ? b->fd_qinv : b->fd_q;
         g.X = fwd ? b->fx_qinv : b->fx_q;
+        g.xs = fwd ? b->fxs_qinv : b->fxs_q;
         g.rot = b->f_rot;
         g.corr = b->f_corr;
     } else g.P = fwd ? b->fs_qinv : b->fs_q;
