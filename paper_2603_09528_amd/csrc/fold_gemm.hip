@@ -19,11 +19,12 @@ __global__ __launch_bounds__(256) void fold_gemm_multi_kernel(const FoldDesc* __
     constexpr int LF = FoldLds<double, Y, true, 16, 64>::TOTAL, LG = SmemF<double, BM, BN, !Y, 16, 2>::TOTAL;
     __shared__ __attribute__((aligned(16))) double smem[LF > LG ? LF : LG];
     __shared__ double red[2 * (256 / 64)];
+    __shared__ unsigned lmax[3 * 64];
     const unsigned gblocks = gridDim.x - fblocks;
     if (blockIdx.x < gblocks)
         gemm_worklist_f<double, double, double, double, EPI_STORE, !Y, BM, BN>(gemm, ngemm, gtiles, smem, red, blockIdx.x, gblocks);
     else
-        fold_tiles<double, double, double, EPI_STORE, Y, INV, true, true, 16, 64, 16, 16>(fold, nfold, coarse, ftiles, smem, red,
+        fold_tiles<double, double, double, EPI_STORE, Y, INV, true, true, 16, 64, 16, 16>(fold, nfold, coarse, ftiles, smem, red, lmax,
                                                                                           blockIdx.x - gblocks, fblocks);
 }
 

@@ -30,6 +30,9 @@
 // and the rotation are the dense basis to the rounding of a double (one term
 // would leave 2e-16 .. 7e-15 on tanh grids); without X, errors of 1e-13 would
 // be left where the dense product has 1e-15.
+// FP32 sums hold fields of any size: a line whose largest value lies outside
+// 2^-60 .. 2^100 has its remainders applied in FP64 instead, element by element
+// after the tile (fold_remainder), so a scaled field has the scaled result.
 //
 // P0, P1 are padded with zero rows and columns (rows to 64, row length to
 // 16), so basis loads need no bounds and the K loop no tail, and stored by
@@ -106,10 +109,39 @@ __device__ __forceinline__ FoldTile fold_find(const FoldDesc* __restrict__ work,
     return t;
 }
 
-// Two BF16 terms of two values (magnitudes past the FP32 range held at its end:
-// a product with a zero remainder stays zero)
-__device__ __forceinline__ void fold_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
-    split_bf16x2(__builtin_amdgcn_fmed3f(a, -3e38f, 3e38f), __builtin_amdgcn_fmed3f(b, -3e38f, 3e38f), hi, lo);
+// The high word of |x|: orders doubles by size, in steps of 2^-20.
+__device__ __forceinline__ unsigned fold_size(double x) {
+    return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32) & 0x7fffffffu;
+}
+// Whether FP32 sums of a line with this largest size can hold its remainders:
+// below 2^100 they don't overflow (the terms of X are below one), above 2^-60
+// what underflows is 2^-66 of them.
+__device__ __forceinline__ bool fold_in_range(unsigned m) {
+    return m == 0 || (m >= (1023u - 60) << 20 && m < (1023u + 100) << 20);
+}
+// The remainders of slot p on a line, in FP64 and from memory: for the rare line
+// out of range.
+template <bool Y, bool INV>
+__device__ __forceinline__ void fold_remainder(const FoldDesc& g, int p, unsigned line, double& ce, double& co) {
+    const unsigned inner = Y ? (unsigned)g.inner : 1u, b = line / inner;
+    const double* in = (const double*)g.in + ((long long)b * inner * g.n + (line - b * inner));
+    ce = co = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < g.h; ++k) {
+        const double r0 = in[(long long)k * inner], r1 = in[(long long)(INV ? g.n - g.h + k : g.n - 1 - k) * inner];
+        double e = r0 + r1, o = r0 - r1;
+        if constexpr (INV) {
+            const double2 r = g.rot[k];
+            e = __builtin_fma(r.x, r0, -(r.y * r1));
+            o = __builtin_fma(r.x, r1, r.y * r0);
+        }
+        const uint16_t* x0 = g.X + ((long long)(k / 8 * 2) * g.hp + p) * 16 + k % 8;
+        const uint16_t* x1 = x0 + (long long)g.hp * 16;
+        ce = __builtin_fma((double)bf16_to_f(x0[0]) + (double)bf16_to_f(x0[8]), o, ce);
+        co = __builtin_fma((double)bf16_to_f(x1[0]) + (double)bf16_to_f(x1[8]), e, co);
+    }
+    ce *= g.xs;
+    co *= g.xs;
 }
 // Eight BF16 values from an 8-byte aligned address
 __device__ __forceinline__ bf16x8 fold_frag(const uint16_t* p) {
@@ -227,7 +259,7 @@ template <typename TM, typename TI, typename TO, int EPI, bool Y, bool INV, bool
           int WP, int WD>
 __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, int nwork,
                                            const unsigned* __restrict__ coarse, unsigned total, TM* smem,
-                                           double* red,
+                                           double* red, [[maybe_unused]] unsigned* lmax,
                                            unsigned block = blockIdx.x, unsigned blocks = gridDim.x) {
     typedef FoldLds<TM, Y, CORR, PH, DN> S;
     static_assert(!CORR || std::is_same<TM, double>::value, "remainders are for FP64");  // (BK = 8)
@@ -314,6 +346,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             rx = __builtin_amdgcn_raw_buffer_load_b64(rX, (int)o.x, (int)((k0 * 2 * g.hp + t.p0 * BK) * 4), 0);
         }
     };
+    [[maybe_unused]] unsigned mx = 0;  // size of the largest value stored of this thread's line
     auto sstore = [&](int buf) {
         TM* P = smem + buf * S::BUF + prow * S::PP + pcol * NK;
         TM* D = smem + buf * S::BUF + 2 * S::P_HALF;
@@ -339,6 +372,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             D[S::D_HALF + o] = b;
             c0[q] = (float)a;
             c1[q] = (float)b;
+            if constexpr (CORR) mx = max(mx, max(fold_size(a), fold_size(b)));
         }
         if constexpr (CORR) {
             uint16_t* C = (uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
@@ -346,7 +380,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             if (NT == 8 * PH || tid < 8 * PH) *(u32x2_t*)(C + 2 * S::B_HALF + prow * S::PB + pcol * 4) = rx;
             uint32_t hi, lo;
             if constexpr (LD == 1) {
-                fold_split2(c0[0], c1[0], hi, lo);
+                split_bf16x2(c0[0], c1[0], hi, lo);
                 B[0] = (uint16_t)hi;
                 B[BK] = (uint16_t)lo;
                 B[S::B_HALF] = (uint16_t)(hi >> 16);
@@ -354,10 +388,10 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             } else {
 #pragma unroll
                 for (int q = 0; q < LD; q += 2) {
-                    fold_split2(c0[q], c0[q + 1], hi, lo);
+                    split_bf16x2(c0[q], c0[q + 1], hi, lo);
                     *(uint32_t*)(B + q) = hi;
                     *(uint32_t*)(B + BK + q) = lo;
-                    fold_split2(c1[q], c1[q + 1], hi, lo);
+                    split_bf16x2(c1[q], c1[q + 1], hi, lo);
                     *(uint32_t*)(B + S::B_HALF + q) = hi;
                     *(uint32_t*)(B + S::B_HALF + BK + q) = lo;
                 }
@@ -382,6 +416,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
     __amdgpu_buffer_rsrc_t rP, rD;
     Offs off;
     setup(lt, rP, rD, off);
+    [[maybe_unused]] int held = 0;       // K step (of its tile) in the registers
     auto load_next = [&]() {
         if (lk == lnk) {
             lk = 0;
@@ -395,13 +430,28 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                 ++ahead;
             }  // else past the last tile: its K steps again, never used
         }
+        held = lk;
         gload(lt, rP, rD, off, lk * BK);
         ++lk;
     };
+    // the lines' sizes go to LDS with the last K step of their tile: three sets,
+    // so that the next tile's may be written, and the one before's cleared,
+    // while a tile's are read
+    [[maybe_unused]] int ws = 0, rs = 0;
+    auto next_set = [](int q) { return q == 2 * DN ? 0 : q + DN; };
     auto stage_held = [&](int buf) {
+        if (CORR && held == 0) mx = 0;
         sstore(buf);
+        if (CORR && held + 1 == lnk) {
+            atomicMax(lmax + ws + dline, mx);
+            ws = next_set(ws);
+        }
         load_next();
     };
+    if constexpr (CORR) {
+        for (int q = tid; q < 3 * DN; q += NT) lmax[q] = 0;
+        __syncthreads();
+    }
     load_next();
     int buf = 0;
     stage_held(0);
@@ -487,18 +537,47 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         if constexpr (CORR) {
             const double xs = g.xs;
             const double2* rot = g.rot + cur.p0 + wp * WP;
+            constexpr int LR = Y ? 1 : 4;  // lines of a lane's results
+            bool ok[MD][LR], all = true;
 #pragma unroll
-            for (int i = 0; i < MP; ++i) {
+            for (int j = 0; j < MD; ++j)
 #pragma unroll
-                for (int j = 0; j < MD; ++j) {
+                for (int r = 0; r < LR; ++r) {
+                    ok[j][r] = fold_in_range(lmax[rs + wd * WD + j * 16 + (Y ? lr : MM::row(lg, r))]);
+                    all = all && ok[j][r];
+                }
+#pragma unroll
+            for (int i = 0; i < MP; ++i)
+#pragma unroll
+                for (int j = 0; j < MD; ++j)
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         const f4 t = fold_transpose(cacc[q][i][j]);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[q][i][j][r] += (double)t[r] * xs;
+                        for (int r = 0; r < 4; ++r) acc[q][i][j][r] += ok[j][r % LR] ? (double)t[r] * xs : 0.0;
                     }
-                    if constexpr (!INV) {
-                        // from the slot's vectors to its eigenvectors
+            if (!all) {
+#pragma unroll
+                for (int i = 0; i < MP; ++i)
+#pragma unroll
+                    for (int j = 0; j < MD; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int p = cur.p0 + wp * WP + i * 16 + (Y ? MM::row(lg, r) : lr);
+                            const unsigned line = cur.d0 + (unsigned)(wd * WD + j * 16 + (Y ? lr : MM::row(lg, r)));
+                            if (ok[j][r % LR] || p >= g.h || line >= (unsigned)g.lines) continue;
+                            double ce, co;
+                            fold_remainder<Y, INV>(g, p, line, ce, co);
+                            acc[0][i][j][r] += ce;
+                            acc[1][i][j][r] += co;
+                        }
+            }
+            if constexpr (!INV) {
+                // from the slot's vectors to its eigenvectors
+#pragma unroll
+                for (int i = 0; i < MP; ++i)
+#pragma unroll
+                    for (int j = 0; j < MD; ++j)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const double2 cs = rot[i * 16 + (Y ? MM::row(lg, r) : lr)];
@@ -506,8 +585,6 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                             acc[0][i][j][r] = __builtin_fma(cs.x, e, cs.y * o);
                             acc[1][i][j][r] = __builtin_fma(cs.x, o, -(cs.y * e));
                         }
-                    }
-                }
             }
         }
         fold_store<TM, TO, EPI, Y, INV, MP, MD>(g, cur, acc, cur.p0 + wp * WP, wd * WD, lr, lg, se, sx);
@@ -519,6 +596,10 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             }
         }
         __syncthreads();
+        if constexpr (CORR) {
+            if (tid < DN) lmax[rs + tid] = 0;  // (used again two tiles on)
+            rs = next_set(rs);
+        }
         buf ^= 1;
         cur = nxt;
         nxt = nxt2;
@@ -534,14 +615,16 @@ TPT_FOLD_TEMPLATE
 __global__ __launch_bounds__((TPT_FOLD_CFG::NT), (TPT_FOLD_CFG::WPE)) void fold_kernel(const FoldDesc g, unsigned total) {
     __shared__ __attribute__((aligned(16))) TM smem[FoldLds<TM, Y, CORR, PH, DN>::TOTAL];
     __shared__ double red[2 * (TPT_FOLD_CFG::NT / 64)];
-    fold_tiles<TM, TI, TO, EPI, Y, INV, CORR, false, PH, DN, WP, WD>(&g, 1, nullptr, total, smem, red);
+    __shared__ unsigned lmax[CORR ? 3 * DN : 1];
+    fold_tiles<TM, TI, TO, EPI, Y, INV, CORR, false, PH, DN, WP, WD>(&g, 1, nullptr, total, smem, red, lmax);
 }
 TPT_FOLD_TEMPLATE
 __global__ __launch_bounds__((TPT_FOLD_CFG::NT), (TPT_FOLD_CFG::WPE)) void fold_multi_kernel(
     const FoldDesc* __restrict__ work, int nwork, const unsigned* __restrict__ coarse, unsigned total) {
     __shared__ __attribute__((aligned(16))) TM smem[FoldLds<TM, Y, CORR, PH, DN>::TOTAL];
     __shared__ double red[2 * (TPT_FOLD_CFG::NT / 64)];
-    fold_tiles<TM, TI, TO, EPI, Y, INV, CORR, true, PH, DN, WP, WD>(work, nwork, coarse, total, smem, red);
+    __shared__ unsigned lmax[CORR ? 3 * DN : 1];
+    fold_tiles<TM, TI, TO, EPI, Y, INV, CORR, true, PH, DN, WP, WD>(work, nwork, coarse, total, smem, red, lmax);
 }
 #undef TPT_FOLD_TEMPLATE
 #undef TPT_FOLD_CFG
