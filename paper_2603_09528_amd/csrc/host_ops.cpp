@@ -117,19 +117,23 @@ std::string build_op1d(int ncells, const double* faces, int bc_lo, int bc_hi, in
     // a Dirichlet mirrored ghost at a cell-centred wall sits at distance dx_1: still uniform
     op.uniform = uni;
     if (per) {
-        op.mirror = op.mirror_exact = uni;
+        op.mirror = uni;
     } else if (bc_lo == bc_hi) {
         // twice the spacing of the doubles just above 1, times the largest
         // coordinate (a tanh-stretched grid has up to 1.3 times)
         const double tol = 2.0 * std::numeric_limits<double>::epsilon() *
                            std::max(std::fabs(faces[0]), std::fabs(faces[ncells]));
-        op.mirror = op.mirror_exact = true;
+        op.mirror = true;
         for (int k = 1; k < ncells; ++k)
             if (!(std::fabs((faces[k] - faces[0]) - (faces[ncells] - faces[ncells - k])) <= tol)) op.mirror = false;
-        for (int k = 0; k < ncells; ++k)
-            if (w[k] != w[ncells - 1 - k]) op.mirror_exact = false;
-        op.mirror_exact = (op.mirror_exact && op.mirror) || uni;
         op.mirror = op.mirror || uni;
+    }
+    // (the closed-form basis of a uniform direction is symmetric: its volumes
+    // have to be, which faces like i / 383 leave to the rounding)
+    op.mirror_exact = op.mirror;
+    for (int i = 0; i < n && op.mirror_exact; ++i) {
+        const int m = n - 1 - i;
+        op.mirror_exact = vol[i] == vol[m] && (uni || (op.b[i] == op.b[m] && op.a[i] == op.c[m]));
     }
     return "";
 }
@@ -495,9 +499,11 @@ bool fold_basis(const Op1D& op, const Eig1D& e, int hp, int kp, FoldBasis& f) {
             f.fwd[half + ak] = (double)(0.5L * (oe - om));
             f.inv[ka] = (double)(0.5L * (ie + im));
             f.inv[half + ka] = (double)(0.5L * (je - jm));
-            xe += 0.5L * (ve[k] - ve[m]) * (ve[k] - ve[m]);
-            xo += (mid ? 0.25L : 0.5L) * (vo[k] + vo[m]) * (vo[k] + vo[m]);
             if (!f.rotated) continue;
+            const real re = std::max(std::fabs(fe - fm) / s[k], std::fabs(ie - im) * s[k]);
+            const real ro = std::max(std::fabs(oe + om) / s[k], std::fabs(je + jm) * s[k]);
+            xe += 0.5L * re * re;
+            xo += (mid ? 0.25L : 0.5L) * ro * ro;
             f.xfwd[ak] = (double)(0.5L * (fe - fm));
             f.xfwd[half + ak] = (double)((mid ? 0.25L : 0.5L) * (oe + om));
             f.xinv[ka] = (double)(0.5L * (je + jm));

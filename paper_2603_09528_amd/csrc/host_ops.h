@@ -23,7 +23,7 @@ struct Op1D {
     // The operator is its own mirror image (i -> n-1-i) up to the rounding of
     // the face coordinates: the same condition at both walls on faces
     // symmetric about the middle, or a uniform periodic direction.  exact:
-    // to the last bit, or a uniform direction (closed-form basis).
+    // to the last bit (of a uniform direction the volumes).
     bool mirror = false, mirror_exact = false;
 };
 

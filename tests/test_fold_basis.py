@@ -38,6 +38,22 @@ def test_stretched_directions_keep_their_eigenvectors(check, grid):
     assert err <= BOUND, err
 
 
+# (no power of two: the faces i / n, and so the volumes, are equal to rounding only)
+UNIFORM = [(383, 0, 0, 1, 2, 0), (383, 0, 3, 1, 2, 0), (96, 0, 0, 3.7, 1, 0), (333, 0, 2, 1, 0, 0), (300, 0, 0, 2, 2, 1), (90, 0, 0, 1, 0, 1)]
+
+
+@pytest.mark.parametrize("grid", UNIFORM, ids=str)
+def test_uniform_directions_keep_their_volumes(check, grid):
+    err, corrected = check(*grid)
+    assert err <= BOUND, err
+    assert corrected
+
+
+def test_symmetric_faces_need_no_remainders(check):
+    assert check(256, 0, 0, 1, 2, 0)[1] is False
+    assert check(96, 0, -48, 96, 1, 0)[1] is False
+
+
 def test_larger_remainders_take_the_whole_basis(check):
     """Remainders past what the two terms hold to a double's rounding."""
     assert check(512, 2.0, 60, 1, 1, 0) is None
