@@ -163,6 +163,7 @@ int plan_gemm_prec(const tpt_plan_s* p);
 
 // Tile selection: autotuned table lookup (falls back to a size heuristic).
 int choose_variant(int prec, int stage_kind, int M, int N, int K);
+// (variant -1: no entry)
 void autotune_record(int prec, int stage_kind, int M, int N, int K, int variant);
 // tuning-table kind of the Thomas kernel entries: (prec, TUNE_THOMAS, lines,
 // nz, 0) -> THOMAS_SEQ or THOMAS_PART + configuration

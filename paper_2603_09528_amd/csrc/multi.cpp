@@ -751,8 +751,8 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
         }
         // Thomas kernel: the automatic choice, the sequential one and every
         // partitioned configuration of a number that fits, on the plan's own
-        // lines (one system); nothing to record where the automatic choice
-        // has no number and is the fastest
+        // lines (one system); where the automatic choice has no number and is
+        // the fastest, no entry: one from before is dropped
         if (!p->op[2].periodic && !p->seq_thomas) {
             const int dt = prec == GP_F64 ? DT_F64 : DT_F32;
             const long long lines = (long long)p->N[0] * p->N[1];
@@ -785,7 +785,7 @@ int tpt_autotune(int count, const tpt_plan* plans, void* stream) {
                         best = v;
                     }
                 }
-                if (best >= 0 && best < THOMAS_PART + THOMAS_NAPI) autotune_record(prec, TUNE_THOMAS, (int)lines, p->N[2], 0, best);
+                if (best >= 0) autotune_record(prec, TUNE_THOMAS, (int)lines, p->N[2], 0, best < THOMAS_PART + THOMAS_NAPI ? best : -1);
                 (void)hipStreamSynchronize(s);
                 (void)hipFree(scratch);
             } else {

@@ -92,7 +92,8 @@ std::string tune_key(int prec, int kind, int M, int N, int K) {
 
 void autotune_record(int prec, int kind, int M, int N, int K, int variant) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    g_tune[tune_key(prec, kind, M, N, K)] = variant;
+    if (variant >= 0) g_tune[tune_key(prec, kind, M, N, K)] = variant;
+    else g_tune.erase(tune_key(prec, kind, M, N, K));
 }
 
 int tuned_thomas(int prec, long long lines, int nz) {
