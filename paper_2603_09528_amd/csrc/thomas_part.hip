@@ -46,26 +46,33 @@ namespace tpt {
 // couplings it leaves fall on the row itself.  A line must end with its last
 // segment then: the rows are dealt out evenly, nz / P or one more to a segment
 // (at most L), the interior takes the first places, the interface row stays in
-// place L-1, and places between are skipped.  The line's data is read once and
+// place L-1, and places between are skipped.
+// Their smooth lines (small |lambda|) are close to singular: what a row's
+// couplings leave of its diagonal is lambda alone, and equal rows, as uniform z
+// has, lose it to the same rounding in every segment.  So the cyclic
+// elimination carries row sums in place of diagonals, here and through the
+// reduction: a pivot is the row's sum less its two couplings, all of one sign,
+// and nothing cancels.
+// The line's data is read once and
 // written once where the sequential kernel reads it three times (two
 // eliminations and the closing) along one chain per line: 256^3, FP64, 56 us
 // against 149.
 // ---------------------------------------------------------------------------
-template <int LB, int P, int L>
+template <int LB, int P, int L, bool CYC>
 struct ThomasPartLds {
     static constexpr int NT = LB * P, CS = L + 1;  // CS: segment stride of cf (one row of bank padding)
     // (A, C, D, E) per row, E = 1 where the line shift applies (0 on identity
-    // rows); segment s at s CS, then the pinned line's copy of segment
+    // rows); CYC: the row's sum A + D + C in place of D; segment s at s CS, then the pinned line's copy of segment
     // (nz-1)/L with row nz-1 made the identity
     double4 cf[(P + 1) * CS];
-    double pcr[2][4][NT];  // interface rows (a, c, d, 1/b) by level; first the up-sweep responses
+    double pcr[2][CYC ? 5 : 4][NT];  // interface rows (a, c, d, 1/b, CYC: sum) by level; first the up-sweep responses
     double zz[P][LB];      // interface solution
 };
 
 // One block of LB lines (block index blk of the problem t with nlines lines).
 template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long nlines, long long blk,
-                                                  ThomasPartLds<LB, P, L>& sh) {
+                                                  ThomasPartLds<LB, P, L, CYC>& sh) {
     constexpr int NT = LB * P, M = L - 1, CS = L + 1, PIN = P * CS;
     constexpr int NE = (P + 1) * L, SI = (NE + NT - 1) / NT;  // staged rows, per thread
     static_assert(L >= 4, "segments need interior rows");
@@ -103,7 +110,13 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
         if (k >= 0 && k < nz && !(seg == P && k == nz - 1)) {
             v.x = CYC || k > 0 ? t.tau * a : 0.0;
             v.y = CYC || k < nz - 1 ? t.tau * c : 0.0;
-            v.z = t.sigma + t.tau * b;
+            if constexpr (CYC) {
+                // a + b + c without the rounding of its parts
+                const double ac = a + c, q = ac - a;
+                v.z = t.sigma + t.tau * ((ac + b) + ((a - (ac - q)) + (c - q)));
+            } else {
+                v.z = t.sigma + t.tau * b;
+            }
             v.w = 1.0;
         }
         sh.cf[seg * CS + r] = v;
@@ -180,48 +193,74 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     // ---- pass 1: end responses of the interior rows 0 .. M-1 ----
     double ip[M];
     double Ud, Vd, Wd, Uu, Vu, Wu;
-    {
+    [[maybe_unused]] double Sd = 0.0, Su = 0.0;  // CYC: responses to the row sums
+    if constexpr (CYC) {
+        // row r after the rows above: coupling lc to the segment's left, sum sg
+        double4 v = cb[0];
+        double lc = v.x, sg = __builtin_fma(v.w, tl, v.z);
+        ip[0] = recip(sg - lc - v.y);
+        double Fd = fv[0] * ip[0], iplast = ip[0];
+#pragma unroll
+        for (int r = 1; r < M; ++r) {
+            ip[r] = 0.0;
+            if (r >= mi) continue;
+            v = cb[r];
+            const double m = v.x * iplast;
+            lc *= -m;
+            sg = __builtin_fma(-m, sg, __builtin_fma(v.w, tl, v.z));
+            ip[r] = recip(sg - lc - v.y);
+            Fd = (fv[r] - v.x * Fd) * ip[r];
+            iplast = ip[r];
+        }
+        Ud = Fd;
+        Vd = 0.0;
+        Wd = -lc * iplast;
+        Sd = sg * iplast;
+        // (as below)
+        asm volatile("" ::: "memory");
+        // row r after the rows below: coupling uc to the interface; the last
+        // interior row has nothing behind it, and uc is its own C
+        double jp = 1.0, Fu = 0.0, uc = -1.0, su = 0.0;
+#pragma unroll
+        for (int r = M - 1; r >= 0; --r) {
+            if (r >= mi) continue;
+            v = cb[r];
+            const double m = v.y * jp;
+            uc *= -m;
+            su = __builtin_fma(-m, su, __builtin_fma(v.w, tl, v.z));
+            jp = recip(su - uc - v.x);
+            Fu = (fv[r] - v.y * Fu) * jp;
+        }
+        Uu = Fu;
+        Vu = -uc * jp;
+        Wu = 0.0;
+        Su = su * jp;
+    } else {
         double4 v = cb[0];
         ip[0] = recip(__builtin_fma(v.w, tl, v.z));
         double Fd = fv[0] * ip[0], Gd = v.x * ip[0], cprev = v.y;
-        [[maybe_unused]] double iplast = ip[0];
 #pragma unroll
         for (int r = 1; r < M; ++r) {
-            if constexpr (CYC) {
-                ip[r] = 0.0;
-                if (r >= mi) continue;
-            }
             v = cb[r];
             ip[r] = recip(__builtin_fma(v.w, tl, v.z) - v.x * cprev * ip[r - 1]);
             Fd = (fv[r] - v.x * Fd) * ip[r];
             Gd = -v.x * Gd * ip[r];
             cprev = v.y;
-            iplast = ip[r];
         }
         Ud = Fd;
-        Vd = -cprev * (CYC ? iplast : ip[M - 1]);
+        Vd = -cprev * ip[M - 1];
         Wd = -Gd;
         // re-read the coefficients rather than keep the down sweep's in
         // registers
         asm volatile("" ::: "memory");
         double jp, Fu, Hu, anext;
-        if constexpr (CYC) {
-            // starts at the last interior row below: with nothing behind it
-            // (anext = 0), its own C as the response to the interface
-            jp = 0.0;
-            Fu = 0.0;
-            Hu = -1.0;
-            anext = 0.0;
-        } else {
-            v = cb[M - 1];
-            jp = recip(__builtin_fma(v.w, tl, v.z));
-            Fu = fv[M - 1] * jp;
-            Hu = v.y * jp;
-            anext = v.x;
-        }
+        v = cb[M - 1];
+        jp = recip(__builtin_fma(v.w, tl, v.z));
+        Fu = fv[M - 1] * jp;
+        Hu = v.y * jp;
+        anext = v.x;
 #pragma unroll
-        for (int r = CYC ? M - 1 : M - 2; r >= 0; --r) {
-            if (CYC && r >= mi) continue;
+        for (int r = M - 2; r >= 0; --r) {
             v = cb[r];
             jp = recip(__builtin_fma(v.w, tl, v.z) - v.y * anext * jp);
             Fu = (fv[r] - v.y * Fu) * jp;
@@ -235,7 +274,8 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     // materialise the responses here: left to the compiler, the products
     // behind Wd and Vd sink past the barrier below with every factor kept
     // in registers
-    asm volatile("" : "+v"(Ud), "+v"(Vd), "+v"(Wd), "+v"(Uu), "+v"(Vu), "+v"(Wu));
+    if constexpr (CYC) asm volatile("" : "+v"(Ud), "+v"(Sd), "+v"(Wd), "+v"(Uu), "+v"(Vu), "+v"(Su));
+    else asm volatile("" : "+v"(Ud), "+v"(Vd), "+v"(Wd), "+v"(Uu), "+v"(Vu), "+v"(Wu));
     // ---- interface system: parallel cyclic reduction over the P rows ----
     // Lane s forms row s (a z_{s-1} + b z_s + c z_{s+1} = d) from its own
     // down-sweep responses and the up-sweep responses of segment s+1; each
@@ -246,49 +286,58 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
     const int me = threadIdx.x;
     sh.pcr[1][0][me] = Uu;
     sh.pcr[1][1][me] = Vu;
-    sh.pcr[1][2][me] = Wu;
+    sh.pcr[1][2][me] = CYC ? Su : Wu;
     __syncthreads();
     double ra, rb, rc, rd;
+    [[maybe_unused]] double rs = 0.0;  // CYC: ra + rb + rc
     {
         const double4 v = cb[M];  // the interface row (pinned copy on the pinned line)
         const double A = v.x, C = v.y;
         ra = A * Wd;
-        rb = __builtin_fma(v.w, tl, v.z) + A * Vd;
+        rb = __builtin_fma(v.w, tl, v.z);
+        if constexpr (!CYC) rb += A * Vd;
         rc = 0.0;
         rd = fv[M] - A * Ud;
         if (CYC || s + 1 < P) {
             const int nb = CYC && s + 1 == P ? l : me + LB;
-            rb += C * sh.pcr[1][2][nb];
+            if constexpr (CYC) rs = rb - A * Sd - C * sh.pcr[1][2][nb];
+            else rb += C * sh.pcr[1][2][nb];
             rc = C * sh.pcr[1][1][nb];
             rd -= C * sh.pcr[1][0][nb];
         }
+        if constexpr (CYC) rb = rs - ra - rc;
     }
     double ib = recip(rb);
 #pragma unroll 1
     for (int h = 1, lvl = 0; h < P; h *= 2, ++lvl) {
-        double (*R)[NT] = sh.pcr[lvl & 1];
+        auto* R = sh.pcr[lvl & 1];
         R[0][me] = ra;
         R[1][me] = rc;
         R[2][me] = rd;
         R[3][me] = ib;
+        if constexpr (CYC) R[4][me] = rs;
         __syncthreads();
-        double na = 0.0, nc = 0.0, nb = rb, nd = rd;
+        double na = 0.0, nc = 0.0, nb = CYC ? rs : rb, nd = rd;
         if (CYC || s >= h) {
             const int u = CYC ? ((s - h) & (P - 1)) * LB + l : me - h * LB;
             const double k1 = ra * R[3][u];
             na = -R[0][u] * k1;
-            nb -= R[1][u] * k1;
+            nb -= R[CYC ? 4 : 1][u] * k1;
             nd -= R[2][u] * k1;
         }
         if (CYC || s + h < P) {
             const int u = CYC ? ((s + h) & (P - 1)) * LB + l : me + h * LB;
             const double k2 = rc * R[3][u];
             nc = -R[1][u] * k2;
-            nb -= R[0][u] * k2;
+            nb -= R[CYC ? 4 : 0][u] * k2;
             nd -= R[2][u] * k2;
         }
-        // (cyclic, last level: both couplings are to the row itself)
-        if (CYC && 2 * h == P) nb += na + nc;
+        if constexpr (CYC) {
+            // from the sum to the diagonal; at the last level both couplings
+            // are to the row itself, and the sum is what multiplies z
+            rs = nb;
+            if (2 * h < P) nb -= na + nc;
+        }
         ra = na;
         rb = nb;
         rc = nc;
@@ -341,7 +390,7 @@ __device__ __forceinline__ void thomas_part_block(const ThomasDesc& t, long long
 
 template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __global__ __launch_bounds__(LB * P) void thomas_part_kernel(ThomasDesc t, long long nlines) {
-    __shared__ ThomasPartLds<LB, P, L> sh;
+    __shared__ ThomasPartLds<LB, P, L, CYC> sh;
     thomas_part_block<LB, P, L, CYC, TF, TX>(t, nlines, blockIdx.x, sh);
 }
 
@@ -351,7 +400,7 @@ __global__ __launch_bounds__(LB * P) void thomas_part_kernel(ThomasDesc t, long 
 template <int LB, int P, int L, bool CYC, typename TF, typename TX>
 __global__ __launch_bounds__(LB * P) void thomas_part_multi_kernel(const ThomasDesc* __restrict__ work, int nwork,
                                                                    long long total_blocks) {
-    __shared__ ThomasPartLds<LB, P, L> sh;
+    __shared__ ThomasPartLds<LB, P, L, CYC> sh;
     for (long long blk = blockIdx.x; blk < total_blocks; blk += gridDim.x) {
         int lo = 0, hi = nwork - 1;
         while (lo < hi) {
