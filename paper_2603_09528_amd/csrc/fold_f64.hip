@@ -29,6 +29,14 @@ long long fold_tiles(FoldDesc& g, int shape) {
     return (long long)g.tiles_p * ((g.lines + dn - 1) / dn);
 }
 
+long long fold_gemm_tiles(FoldDesc& g, int shape) {
+    int ph, dn;
+    fold_dims(g, shape, &ph, &dn);
+    if (shape == FOLD_32x128 && g.corr) dn = 64;
+    g.tiles_p = (g.h + ph - 1) / ph;
+    return (long long)g.tiles_p * ((g.lines + dn - 1) / dn);
+}
+
 static int fold_shapes(int prec) { return prec == GP_BF16X3 ? 2 : (int)FOLD_NSHAPE; }
 
 long long fold_max_tiles(int n, long long lines, int prec) {

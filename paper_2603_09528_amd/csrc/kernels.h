@@ -146,6 +146,7 @@ inline int fold_cols(int prec) { return prec == GP_BF16X3 ? 32 : FOLD_COLS; }
 // every shape gives the same bits).
 int fold_shape(const FoldDesc* g, int count);
 long long fold_tiles(FoldDesc& g, int shape);       // sets tiles_p; the tile count
+long long fold_gemm_tiles(FoldDesc& g, int shape);  // of launch_fold_gemm: 32 x 64 with remainders for 32 x 128
 // The most tiles that any shape makes of x lines of n unknowns (no remainders).
 long long fold_max_tiles(int n, long long lines, int prec);
 // Blocks of a launch of `total` tiles: at most what the GPU holds at once (two
@@ -160,10 +161,11 @@ std::vector<unsigned> fold_coarse(const std::vector<FoldDesc>& g, long long tota
 hipError_t launch_fold(FoldDesc g, hipStream_t s);
 hipError_t launch_fold_multi(const FoldDesc& rep, const FoldList& list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f64(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
-// tiles (16 x 64, remainders applied) of the list and the FP64 work-list tiles of
-// the same stage
-hipError_t launch_fold_gemm(const FoldDesc& rep, const FoldList& list, long long ftiles, const GemmDesc* gemm, int ngemm,
-                            long long gtiles, hipStream_t s);
+// The tiles of the list and the FP64 or FP32 work-list tiles of the same stage
+// (FP64: remainders applied).  shape: FOLD_32x128 (FP64: tiles of 32 x 64,
+// fold_gemm_tiles), or FOLD_16x64 (FP32).
+hipError_t launch_fold_gemm(const FoldDesc& rep, const FoldList& list, long long ftiles, int shape, const GemmDesc* gemm,
+                            int ngemm, long long gtiles, hipStream_t s);
 hipError_t launch_fold_bf16(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 hipError_t launch_fold_f32(const FoldDesc& g, const FoldList* list, long long total, int shape, hipStream_t s);
 

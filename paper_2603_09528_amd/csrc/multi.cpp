@@ -160,12 +160,15 @@ int MultiExec::add_gemm_stage(int stage, int prec, const std::vector<GemmDesc>& 
 // us a batch apart, 1095 up to 512 tiles, 1074 up to 2048; ten requests of 64
 // to 256, 2240, 2230, 2216, and 2370 always together.
 constexpr long long FOLD_MERGE = 2048;
-// Tiles of either kind up to which a stage's half-size products (16 x 64) share
-// a launch with its work-list GEMM: a batch of 12 problems of 29 to 100 cells a
-// direction 261 us apart and 241 joined, of 18 of 31 to 98, 333 and 315; larger
-// ones lose by the small tile (ten requests of 64 to 256, always joined: 2345
-// against 2190).
-constexpr long long FOLD_JOIN = 3072;
+// A stage whose whole products are one work list takes its half-size products
+// into that launch (fold_gemm.hip); us a batch, in two launches
+// and in one: twelve problems of 29 to 100 cells a direction 188 and 155 (FP32
+// with two corrections 485 and 384), twenty of 40 to 120 409 and 343, sixteen
+// of 48 to 192 1121 and 1066, six of 150 to 260 2162 and 2062, four of 200 to
+// 300 3495 and 3497; ten requests of 64 to 256 2200 and 2220.  FP32 in tiles of
+// 16 x 64 while every tile has a block of its own: five problems of 24 to 40,
+// 188 against 191; FP64 is as fast or faster in the larger one there (84 and 88).
+constexpr long long FOLD_JOIN_SMALL = 768;
 
 int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const std::vector<char>& use,
                               std::vector<long long>* nb, bool with_gemm) {
@@ -182,8 +185,11 @@ int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const s
             small += fold_tiles(g, FOLD_16x64);
         }
     // with_gemm: the stage's only other launch is a work-list GEMM
-    const bool join = with_gemm && prec == GP_F64 && small > 0 && small <= FOLD_JOIN && seq_.back().total <= FOLD_JOIN;
-    const bool merge = join || tiles[0] > 0 && tiles[1] > 0 && std::min(tiles[0], tiles[1]) <= FOLD_MERGE;
+    // (FP64 joins with remainders applied: not many tiles that have none)
+    const bool join = with_gemm && small > 0 && (prec == GP_F32 || (prec == GP_F64 && tiles[0] <= FOLD_MERGE));
+    const bool join_small = join && prec == GP_F32 && small + seq_.back().total <= FOLD_JOIN_SMALL;
+    const bool merge =
+        (join && prec == GP_F64) || (tiles[0] > 0 && tiles[1] > 0 && std::min(tiles[0], tiles[1]) <= FOLD_MERGE);
     for (int corr = merge ? 1 : 0; corr < 2; ++corr) {
         std::vector<FoldDesc> grp;
         std::vector<size_t> idx;
@@ -194,10 +200,10 @@ int MultiExec::add_fold_stage(int prec, const std::vector<FoldDesc>& gs, const s
             idx.push_back(i);
         }
         if (grp.empty()) continue;
-        const int shape = join ? (int)FOLD_16x64 : fold_shape(grp.data(), (int)grp.size());
+        const int shape = join_small ? (int)FOLD_16x64 : join ? (int)FOLD_32x128 : fold_shape(grp.data(), (int)grp.size());
         long long total = 0;
         for (size_t k = 0; k < grp.size(); ++k) {
-            const long long t = fold_tiles(grp[k], shape);
+            const long long t = join ? fold_gemm_tiles(grp[k], shape) : fold_tiles(grp[k], shape);
             grp[k].block_begin = total;
             total += t;
             if (nb) (*nb)[idx[k]] = t;
@@ -486,7 +492,7 @@ int MultiExec::enqueue(hipStream_t s) const {
                 TimedScope ts("multi_gemm", s);
                 const FoldDesc& rep = *(const FoldDesc*)(blob_.data() + L.off);
                 const FoldList list{(const FoldDesc*)(d_desc_ + L.off), L.nwork, (const unsigned*)(d_desc_ + L.off2)};
-                e = launch_fold_gemm(rep, list, L.total, (const GemmDesc*)(d_desc_ + L.off3), L.nwork3, L.total3, s);
+                e = launch_fold_gemm(rep, list, L.total, L.variant, (const GemmDesc*)(d_desc_ + L.off3), L.nwork3, L.total3, s);
                 break;
             }
             case 8: {
