@@ -59,14 +59,15 @@ namespace tpt {
 // lines) or [parity][DN][BK] (x lines), rows padded by 16 bytes.
 // CORR keeps the remainders, [parity][PH][16], and the data's BF16 copies,
 // [parity][DN][16], a row the high terms of the step's columns and then the low
-// ones, rows padded to 40 bytes.
+// ones, the other way round in every second eight rows: sixteen rows' high (or
+// low) terms, read together, then lie in different banks.
 template <typename TM, bool Y, bool CORR, int PH, int DN> struct FoldLds {
     static constexpr int BK = 64 / (int)sizeof(TM), NK = BK / 4;
     static constexpr int PP = BK + NK;
     static constexpr int PD = Y ? DN * NK : BK + NK;
     static constexpr int P_HALF = PH * PP, D_HALF = (Y ? 4 : DN) * PD;
     static constexpr int BUF = 2 * (P_HALF + D_HALF);
-    static constexpr int PB = 20, B_HALF = DN * PB, X_HALF = PH * PB;  // in bf16
+    static constexpr int PB = 16, B_HALF = DN * PB, X_HALF = PH * PB;  // in bf16
     static constexpr int B_BUF = 2 * (B_HALF + X_HALF);
     static constexpr int TOTAL = 2 * BUF + (CORR ? 2 * B_BUF * 2 / (int)sizeof(TM) : 0);
 };
@@ -143,11 +144,9 @@ __device__ __forceinline__ void fold_remainder(const FoldDesc& g, int p, unsigne
     ce *= g.xs;
     co *= g.xs;
 }
-// Eight BF16 values from an 8-byte aligned address
-__device__ __forceinline__ bf16x8 fold_frag(const uint16_t* p) {
-    const u32x2_t a = *(const u32x2_t*)p, b = *(const u32x2_t*)(p + 4);
-    return __builtin_bit_cast(bf16x8, (u32x4_t){a[0], a[1], b[0], b[1]});
-}
+// Offset in its row of the high (t = 0) or low (t = 1) terms.
+__device__ __forceinline__ int fold_term(int row, int t) { return ((row >> 3) & 1) == t ? 0 : 8; }
+__device__ __forceinline__ bf16x8 fold_frag(const uint16_t* p) { return __builtin_bit_cast(bf16x8, *(const u16x8*)p); }
 
 // The FP32 MFMA leaves rows 4 g + r of a 16 x 16 result in lane group g (of
 // 16 lanes), register r; the FP64 one rows g + 4 r.  Transposing (g, r) makes
@@ -376,24 +375,26 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         }
         if constexpr (CORR) {
             uint16_t* C = (uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
-            uint16_t* B = C + dline * S::PB + dk;
-            if (NT == 8 * PH || tid < 8 * PH) *(u32x2_t*)(C + 2 * S::B_HALF + prow * S::PB + pcol * 4) = rx;
+            uint16_t* B = C + dline * S::PB + dk + fold_term(dline, 0);
+            uint16_t* D = C + dline * S::PB + dk + fold_term(dline, 1);
+            if (NT == 8 * PH || tid < 8 * PH)
+                *(u32x2_t*)(C + 2 * S::B_HALF + prow * S::PB + fold_term(prow, pcol >> 1) + (pcol & 1) * 4) = rx;
             uint32_t hi, lo;
             if constexpr (LD == 1) {
                 split_bf16x2(c0[0], c1[0], hi, lo);
                 B[0] = (uint16_t)hi;
-                B[BK] = (uint16_t)lo;
+                D[0] = (uint16_t)lo;
                 B[S::B_HALF] = (uint16_t)(hi >> 16);
-                B[S::B_HALF + BK] = (uint16_t)(lo >> 16);
+                D[S::B_HALF] = (uint16_t)(lo >> 16);
             } else {
 #pragma unroll
                 for (int q = 0; q < LD; q += 2) {
                     split_bf16x2(c0[q], c0[q + 1], hi, lo);
                     *(uint32_t*)(B + q) = hi;
-                    *(uint32_t*)(B + BK + q) = lo;
+                    *(uint32_t*)(D + q) = lo;
                     split_bf16x2(c1[q], c1[q + 1], hi, lo);
                     *(uint32_t*)(B + S::B_HALF + q) = hi;
-                    *(uint32_t*)(B + S::B_HALF + BK + q) = lo;
+                    *(uint32_t*)(D + S::B_HALF + q) = lo;
                 }
             }
         }
@@ -507,11 +508,13 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
 #pragma unroll
             for (int kk = NK / 2; kk < NK; ++kk) multiply(kk);
             if constexpr (CORR) {
+                // (moved up between the MFMAs above, their operands would spill)
+                __builtin_amdgcn_sched_barrier(0);
                 // K = 32: the columns by (high, low, high, low) terms of the
                 // remainders and (high, high, low, low) ones of the data
                 const uint16_t* C = (const uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
-                const uint16_t* B = C + (wd * WD + lr) * S::PB + (lg >> 1) * BK;
-                const uint16_t* X = C + 2 * S::B_HALF + (wp * WP + lr) * S::PB + (lg & 1) * BK;
+                const uint16_t* B = C + (wd * WD + lr) * S::PB + fold_term(lr, lg >> 1);
+                const uint16_t* X = C + 2 * S::B_HALF + (wp * WP + lr) * S::PB + fold_term(lr, lg & 1);
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     bf16x8 xv[MP];
