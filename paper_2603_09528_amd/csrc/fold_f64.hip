@@ -53,20 +53,22 @@ long long fold_max_tiles(int n, long long lines, int prec) {
 // Relative time of a launch of `tiles` tiles: what the compute unit with most
 // tiles has to do, over the rate the shape reaches when it has enough.  The
 // padding of h to whole tiles and the idle units of a last round are in the
-// tile count.  Rates from 256^3, 448 x 320 x 288 and 640 x 640 x 64 (remainders:
-// 40, 35 and 23 TFLOP/s useful for 64 x 64, 32 x 128 and 16 x 64; without:
-// 46, 45 and 36); cases it decides, with remainders: 448 x 320 x 288 in 32 x 128,
-// y 386 and 407 us (403 and 417 in 64 x 64), x, near its edge, 513 and 561 (518
-// and 535); 192 x 160 x 128, x lines, 34 us in 32 x 128 against 40 in 64 x 64;
-// 64 x 48 x 64, 6-9 us in 16 x 64 against 7-11.  Without: 192 x 160 x 128, x lines, 26 against 38
-// us in 64 x 128.
+// tile count.  Rates from 256^3, 448 x 320 x 288, 512 x 383 x 256 and 640 x 640
+// x 64 (64 x 64, 32 x 128 and 16 x 64 with remainders: 39, 34 and 23 TFLOP/s
+// useful forward, 37, 31 and 20 inverse; 64 x 128, 32 x 128 and 16 x 64 without:
+// 46, 45 and 36).  Cases it decides, with remainders: 448 x 320 x 288, x inverse
+// 559 us in 64 x 64 against 599 in 32 x 128, y forward 414 against 399; 192 x 160
+// x 128, x lines, 33-35 us in 32 x 128 against 39; 64 x 48 x 64, 5-7 us in 16 x
+// 64 against 7-11.  Without: 192 x 160 x 128, x lines, 26 against 38 us in
+// 64 x 128.
 // Split BF16, 64 x 128 and 32 x 64: 128^3, 6.3-9.4 and 5.7-7.7 us; 256 x 200 x 100,
 // x 17-19 and 16-17, y 14 and 17.
 static double fold_cost(const FoldDesc& g, int shape, long long tiles) {
-    static const double rate[3][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.87, 0.58}, {1.0, 0.7, 0.0}};
+    // without remainders, with (forward, inverse), split BF16
+    static const double rate[4][FOLD_NSHAPE] = {{1.0, 0.97, 0.78}, {1.0, 0.89, 0.58}, {1.0, 0.83, 0.55}, {1.0, 0.7, 0.0}};
     int ph, dn;
     fold_dims(g, shape, &ph, &dn);
-    return (double)((tiles + 255) / 256) * ph * dn / rate[g.prec == GP_BF16X3 ? 2 : g.corr][shape];
+    return (double)((tiles + 255) / 256) * ph * dn / rate[g.prec == GP_BF16X3 ? 3 : g.corr ? 1 + g.inverse : 0][shape];
 }
 
 int fold_shape(const FoldDesc* g, int count) {

@@ -30,9 +30,10 @@
 // and the rotation are the dense basis to the rounding of a double (one term
 // would leave 2e-16 .. 7e-15 on tanh grids); without X, errors of 1e-13 would
 // be left where the dense product has 1e-15.
-// FP32 sums hold fields of any size: a line whose largest value lies outside
-// 2^-60 .. 2^100 has its remainders applied in FP64 instead, element by element
-// after the tile (fold_remainder), so a scaled field has the scaled result.
+// FP32 sums hold fields of any size: a tile with a line whose largest value lies
+// outside 2^-90 .. 2^100 is multiplied again, with the copies of such a line over
+// a power of two (its largest exponent), so a scaled field has the scaled result.
+// Whether and how is up to the line alone: every tile shape gives the same bits.
 //
 // P0, P1 are padded with zero rows and columns (rows to 64, row length to
 // 16), so basis loads need no bounds and the K loop no tail, and stored by
@@ -114,35 +115,13 @@ __device__ __forceinline__ FoldTile fold_find(const FoldDesc* __restrict__ work,
 __device__ __forceinline__ unsigned fold_size(double x) {
     return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32) & 0x7fffffffu;
 }
-// Whether FP32 sums of a line with this largest size can hold its remainders:
-// below 2^100 they don't overflow (the terms of X are below one), above 2^-60
-// what underflows is 2^-66 of them.
-__device__ __forceinline__ bool fold_in_range(unsigned m) {
-    return m == 0 || (m >= (1023u - 60) << 20 && m < (1023u + 100) << 20);
-}
-// The remainders of slot p on a line, in FP64 and from memory: for the rare line
-// out of range.
-template <bool Y, bool INV>
-__device__ __forceinline__ void fold_remainder(const FoldDesc& g, int p, unsigned line, double& ce, double& co) {
-    const unsigned inner = Y ? (unsigned)g.inner : 1u, b = line / inner;
-    const double* in = (const double*)g.in + ((long long)b * inner * g.n + (line - b * inner));
-    ce = co = 0.0;
-#pragma unroll 1
-    for (int k = 0; k < g.h; ++k) {
-        const double r0 = in[(long long)k * inner], r1 = in[(long long)(INV ? g.n - g.h + k : g.n - 1 - k) * inner];
-        double e = r0 + r1, o = r0 - r1;
-        if constexpr (INV) {
-            const double2 r = g.rot[k];
-            e = __builtin_fma(r.x, r0, -(r.y * r1));
-            o = __builtin_fma(r.x, r1, r.y * r0);
-        }
-        const uint16_t* x0 = g.X + ((long long)(k / 8 * 2) * g.hp + p) * 16 + k % 8;
-        const uint16_t* x1 = x0 + (long long)g.hp * 16;
-        ce = __builtin_fma((double)bf16_to_f(x0[0]) + (double)bf16_to_f(x0[8]), o, ce);
-        co = __builtin_fma((double)bf16_to_f(x1[0]) + (double)bf16_to_f(x1[8]), e, co);
-    }
-    ce *= g.xs;
-    co *= g.xs;
+// The power of two over which a line with this largest size has its remainders
+// formed: below 2^100 FP32 sums don't overflow (the terms of X / xs are below
+// one), above 2^-90 what underflows is 2^-36 of them.  (Zero has none; infinities
+// and NaN are lost on the line anyway.)
+__device__ __forceinline__ int fold_shift(unsigned m) {
+    const bool in = m == 0 || m >= 0x7ff00000u || (m >= (1023u - 90) << 20 && m < (1023u + 100) << 20);
+    return in ? 0 : (int)(m >> 20) - 1023;
 }
 // Offset in its row of the high (t = 0) or low (t = 1) terms.
 __device__ __forceinline__ int fold_term(int row, int t) { return ((row >> 3) & 1) == t ? 0 : 8; }
@@ -346,6 +325,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         }
     };
     [[maybe_unused]] unsigned mx = 0;  // size of the largest value stored of this thread's line
+    [[maybe_unused]] int sh = 0;       // less the power of two of its copies
     auto sstore = [&](int buf) {
         TM* P = smem + buf * S::BUF + prow * S::PP + pcol * NK;
         TM* D = smem + buf * S::BUF + 2 * S::P_HALF;
@@ -369,9 +349,11 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             }
             D[o] = a;
             D[S::D_HALF + o] = b;
-            c0[q] = (float)a;
-            c1[q] = (float)b;
-            if constexpr (CORR) mx = max(mx, max(fold_size(a), fold_size(b)));
+            if constexpr (CORR) {
+                c0[q] = (float)__builtin_ldexp(a, sh);
+                c1[q] = (float)__builtin_ldexp(b, sh);
+                mx = max(mx, max(fold_size(a), fold_size(b)));
+            }
         }
         if constexpr (CORR) {
             uint16_t* C = (uint16_t*)(smem + 2 * S::BUF) + buf * S::B_BUF;
@@ -439,15 +421,19 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
     // so that the next tile's may be written, and the one before's cleared,
     // while a tile's are read
     [[maybe_unused]] int ws = 0, rs = 0;
+    [[maybe_unused]] bool again = false;  // the tile's second time
     auto next_set = [](int q) { return q == 2 * DN ? 0 : q + DN; };
     auto stage_held = [&](int buf) {
-        if (CORR && held == 0) mx = 0;
         sstore(buf);
         if (CORR && held + 1 == lnk) {
             atomicMax(lmax + ws + dline, mx);
             ws = next_set(ws);
         }
         load_next();
+    };
+    auto stage = [&](int buf) {
+        if (CORR && held == 0) mx = sh = 0;  // the next tile's first
+        stage_held(buf);
     };
     if constexpr (CORR) {
         for (int q = tid; q < 3 * DN; q += NT) lmax[q] = 0;
@@ -457,7 +443,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
     int buf = 0;
     stage_held(0);
     __syncthreads();
-    for (; v < total; v += grid) {
+    while (v < total) {
         const FoldDesc& g = desc(cur);
         const int nk = (g.h + BK - 1) / BK;
         typename MM::acc acc[2][MP][MD];
@@ -504,7 +490,7 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             // the next K step goes to the other buffer between the two halves of
             // the MFMAs, so that the wait for its loads overlaps them, and the
             // loads of the one after it are issued
-            stage_held(buf ^ 1);
+            stage(buf ^ 1);
 #pragma unroll
             for (int kk = NK / 2; kk < NK; ++kk) multiply(kk);
             if constexpr (CORR) {
@@ -541,14 +527,40 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
             const double xs = g.xs;
             const double2* rot = g.rot + cur.p0 + wp * WP;
             constexpr int LR = Y ? 1 : 4;  // lines of a lane's results
-            bool ok[MD][LR], all = true;
+            bool out = false;  // (the same answer in every wave)
+#pragma unroll
+            for (int q = 0; q < DN; q += 64) out = out || fold_shift(lmax[rs + q + l]) != 0;
+            double f[MD][LR];
 #pragma unroll
             for (int j = 0; j < MD; ++j)
 #pragma unroll
-                for (int r = 0; r < LR; ++r) {
-                    ok[j][r] = fold_in_range(lmax[rs + wd * WD + j * 16 + (Y ? lr : MM::row(lg, r))]);
-                    all = all && ok[j][r];
+                for (int r = 0; r < LR; ++r) f[j][r] = xs;
+            if (__builtin_expect(__any(out) != 0, 0)) {
+                if (!again) {
+                    // back to the tile's first K step
+                    __syncthreads();
+                    again = true;
+                    mx = 0;
+                    sh = -fold_shift(lmax[rs + dline]);
+                    if (tid < DN) lmax[next_set(rs) + tid] = 0;  // (the next tile may have been here)
+                    ws = rs;
+                    lv = v;
+                    lt = cur;
+                    lk = 0;
+                    lnk = nk;
+                    ahead = 0;
+                    setup(lt, rP, rD, off);
+                    load_next();
+                    stage_held(buf);
+                    __syncthreads();
+                    continue;
                 }
+#pragma unroll
+                for (int j = 0; j < MD; ++j)
+#pragma unroll
+                    for (int r = 0; r < LR; ++r)
+                        f[j][r] = ldexp(xs, fold_shift(lmax[rs + wd * WD + j * 16 + (Y ? lr : MM::row(lg, r))]));
+            }
 #pragma unroll
             for (int i = 0; i < MP; ++i)
 #pragma unroll
@@ -557,24 +569,8 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
                     for (int q = 0; q < 2; ++q) {
                         const f4 t = fold_transpose(cacc[q][i][j]);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[q][i][j][r] += ok[j][r % LR] ? (double)t[r] * xs : 0.0;
+                        for (int r = 0; r < 4; ++r) acc[q][i][j][r] += (double)t[r] * f[j][r % LR];
                     }
-            if (!all) {
-#pragma unroll
-                for (int i = 0; i < MP; ++i)
-#pragma unroll
-                    for (int j = 0; j < MD; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int p = cur.p0 + wp * WP + i * 16 + (Y ? MM::row(lg, r) : lr);
-                            const unsigned line = cur.d0 + (unsigned)(wd * WD + j * 16 + (Y ? lr : MM::row(lg, r)));
-                            if (ok[j][r % LR] || p >= g.h || line >= (unsigned)g.lines) continue;
-                            double ce, co;
-                            fold_remainder<Y, INV>(g, p, line, ce, co);
-                            acc[0][i][j][r] += ce;
-                            acc[1][i][j][r] += co;
-                        }
-            }
             if constexpr (!INV) {
                 // from the slot's vectors to its eigenvectors
 #pragma unroll
@@ -602,11 +598,13 @@ __device__ __forceinline__ void fold_tiles(const FoldDesc* __restrict__ work, in
         if constexpr (CORR) {
             if (tid < DN) lmax[rs + tid] = 0;  // (used again two tiles on)
             rs = next_set(rs);
+            again = false;
         }
         buf ^= 1;
         cur = nxt;
         nxt = nxt2;
         --ahead;
+        v += grid;
     }
 }
 

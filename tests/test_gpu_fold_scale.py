@@ -69,3 +69,20 @@ def test_lines_of_every_size_agree_between_tiles():
     torch.cuda.synchronize()
     for o, s in zip(outs, singles):
         assert np.array_equal(host(o), s)
+
+
+def test_infinite_and_nan_lines_stay_where_they_are():
+    """y lines alone (implicit y and z on one plane): a line that holds an
+    infinity or a NaN has no finite result, and no other line changes."""
+    T = _T()
+    p = W.make_problem((96, 72, 2), (1.0, 2.0, 1.0), (W.PP, W.NN, W.DD), kind="helmholtz", alpha=1e-6)
+    f = W.rhs(p, 41)
+    plan = T.Plan.from_problem(p, implicit="yz")
+    one = host(plan.solve(cuda(f)))
+    bad = f.copy()
+    bad[1, 5, 3], bad[0, 70, 40], bad[1, 36, 64] = np.inf, np.nan, -np.inf
+    got = host(plan.solve(cuda(bad)))
+    lines = np.zeros(p.n[0], bool)
+    lines[[3, 40, 64]] = True
+    assert not np.isfinite(got[:, :, lines]).all(axis=(0, 1)).any()
+    assert np.array_equal(got[:, :, ~lines], one[:, :, ~lines])
