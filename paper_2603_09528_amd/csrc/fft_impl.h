@@ -32,10 +32,11 @@ __host__ __device__ inline int ut_threads(int n, bool wide = false) { return ut_
 // three, so that the lanes of strided (y) lines, which run across lines,
 // fall in different banks
 __host__ __device__ inline int ut_line_stride(int n) { return (n >> 1) + (n >> 5) + 3; }
-// Wide blocks of 1024 and more leave the quarter-wave table in memory: two
-// blocks then fit a compute unit (at 512 they fit with it, and the inverse DCT
-// takes 58 instead of 65 us at 256 x 512 x 128).
-__host__ __device__ constexpr bool ut_qmem(int n, bool wide) { return wide && n >= 1024; }
+// Wide blocks of 1024 leave the quarter-wave table in memory: two blocks then
+// fit a compute unit.  At 512 they fit with it, and the inverse DCT takes 58
+// instead of 65 us at 256 x 512 x 128; at 2048 one block fits either way, and the
+// inverse takes 275 instead of 284 us at 512 x 2048 x 32 (forward 258 and 254).
+__host__ __device__ constexpr bool ut_qmem(int n, bool wide) { return wide && n == 1024; }
 __host__ __device__ inline size_t ut_lds_bytes(int n, bool wide = false) {
     // line data, then W (N/2 entries) and the quarter-wave table (N/2 + 1)
     const size_t tab = ut_qmem(n, wide) ? (size_t)n / 2 : (size_t)n + 1;
