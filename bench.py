@@ -92,18 +92,17 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("kernels.hip", "thomas_part.hip", "fft.hip", "fft_multi.hip", "fft_impl.h", "fft_core.h", "xgemm.hip",
-                  "gemm_f64.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_impl.h", "mfma_tile.h", "fold_f64.hip",
-                  "fold_f32.hip", "fold_bf16.hip", "fold_impl.h", "device_common.h", "kernels.h")
+CSRC = os.path.join(ROOT, "paper_2603_09528_amd", "csrc")
 
 
 def kernel_hash():
     """Hash of every device-code source (the counters in profiles/traffic.json
     are only valid for the kernels they were taken on)."""
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_2603_09528_amd", "csrc", name), "rb") as fh:
-            h.update(fh.read())
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".h")):
+            with open(os.path.join(CSRC, name), "rb") as fh:
+                h.update(fh.read())
     return h.hexdigest()[:16]
 
 
@@ -188,7 +187,9 @@ PAPER_1024_VARIANT_S = {"FF": 0.094, "FG": 0.163, "GF": 0.199, "GG": 0.267}
 def run_variants(args, T, W):
     """The paper's transform-variant comparison on one GPU: the uniform
     n^3 Poisson problem (periodic x, Neumann y and z) in FP64 with x and y
-    each by fast transform (F) or dense GEMM (G)."""
+    each by fast transform (F) or products with its eigenbasis (G; of half the
+    size here, the directions being their own mirror images: half the
+    multiplications of the paper's G)."""
     import torch
     n = args.variants_n
     prob = W.make_problem((n, n, n), (0.0, 0.0, 0.0), (W.PP, W.NN, W.NN), name=f"uniform{n}_pnn")
@@ -204,6 +205,7 @@ def run_variants(args, T, W):
         return float(np.linalg.norm(d) / np.linalg.norm(ref - ref.mean()))
 
     res = {"workload": f"{n}^3 Poisson, periodic x, Neumann y and z, uniform, FP64", "dof": prob.dof,
+           "products": "half-size (mirror-symmetric directions)",
            "paper_gb200_s": PAPER_1024_VARIANT_S if n == 1024 else None}
     for name, dx, dy in (("FF", False, False), ("FG", False, True), ("GF", True, False), ("GG", True, True)):
         t0 = time.time()
@@ -476,7 +478,8 @@ def run_slab(args, T, W):
 def run_ns(args, T, W):
     """Cost of a complete Navier-Stokes time step (the three Runge-Kutta
     substeps of Eq. rk3) against the Poisson solve alone, with the pressure
-    solved by fast transforms in x and y (FF) or by dense GEMMs (GG): the
+    solved by fast transforms in x and y (FF) or by eigenbasis products of half
+    the size (GG): the
     n^3 grid of the transform-variant comparison (periodic x, walls in y and
     z, uniform), FP64.  Diffusion explicit (the pressure is the only
     elliptic solve; both variants) and implicit in x, y and z (FF, the

@@ -83,8 +83,9 @@ enum {
     TPT_FLAG_HOST_ONLY = 1, /* build the host-side operators and eigenbases
                                only (no device memory, no GPU needed); such a
                                plan can be inspected but not solved */
-    TPT_FLAG_DENSE_X = 2,   /* apply the x eigenbasis by dense GEMM even where a
-                               fast transform applies (see tpt_plan_transforms) */
+    TPT_FLAG_DENSE_X = 2,   /* apply the x eigenbasis by matrix products even
+                               where a fast transform applies (see
+                               tpt_plan_transforms) */
     TPT_FLAG_DENSE_Y = 4,   /* the same for y */
     TPT_FLAG_FUSE_XY = 8,   /* FP64 plans whose x is a fast transform and y a
                                GEMM: run the two as one fused pass per
@@ -104,7 +105,11 @@ enum {
 
 /* How a plan applies the eigenbasis of x or y (tpt_plan_transforms). */
 enum {
-    TPT_XFORM_GEMM = 0,     /* dense eigenbasis product (MFMA GEMM) */
+    TPT_XFORM_GEMM = 0,     /* eigenbasis products (MFMA): with the whole basis, or,
+                               in a direction of 16 or more unknowns that is its own
+                               mirror image (equal conditions at both walls on faces
+                               symmetric to rounding; uniform periodic), two of half
+                               the size with its even and odd halves */
     TPT_XFORM_FFT = 1,      /* uniform periodic: real Fourier transform */
     TPT_XFORM_DCT = 2,      /* uniform Neumann-Neumann, cell centres: DCT-II */
     TPT_XFORM_DST = 3,      /* uniform Dirichlet-Dirichlet, cell centres: DST-II */
@@ -336,7 +341,9 @@ int tpt_batch_info(tpt_batch batch, int index, tpt_info *info);
 /* ---- autotuning of GEMM tiles and the Thomas kernel ------------------------ */
 
 /* Time every compiled tile variant for the GEMM shapes of the given plans and
- * record the fastest per (shape class, precision) in the process-wide table;
+ * record the fastest per (shape class, precision) in the process-wide table
+ * (directions with whole-basis products; half-size products choose their tile
+ * by a rule and have no entries);
  * for non-periodic z, likewise time the sequential and the partitioned Thomas
  * kernels (variants of tpt_thomas) on the plan's lines and record the fastest
  * per (precision, line count, line length).  Plans created before or after

@@ -180,8 +180,9 @@ class Plan:
     'helmholtz' with alpha; implicit 'xyz', 'yz' or 'z' (Helmholtz: the
     directions in the implicit operator); precision 'fp64', 'fp32' or 'bf16x3';
     fixed_refine >= 0 runs that many corrections without host synchronisation;
-    dense_x / dense_y force the dense GEMM for a direction where a fast
-    transform (FFT, DCT-II, DST-II of a uniform direction) would apply;
+    dense_x / dense_y force matrix products with the eigenbasis (of half the
+    size where the direction is its own mirror image) where a fast transform
+    (FFT, DCT-II, DST-II of a uniform direction) would apply;
     fuse_xy runs the x fast transform and the y GEMM of an FP64 solve as
     one fused pass per direction (see `fused`; slower on gfx950 than the
     separate passes, so off by default); seq_thomas solves the z lines with
